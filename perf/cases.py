@@ -13,6 +13,7 @@ isotropic population in a weakly perturbed field (gyration test), the power-law
 band of the shock strip, and the shock wall's precursor.
 """
 import math
+import random
 
 import torch
 
@@ -223,13 +224,22 @@ def _single(case, g):
                 rho=rho, dt=[dt])
 
 
+def _batch_shapes(case):
+    """(nx, ny, particles per cell) of each box: the case's geometry, sides
+    log-uniform in [nx, ny], particles per cell log-uniform in [ppc/4, 4 ppc]."""
+    rng = random.Random(1000 * case["boxes"] + case["ny"])
+    out = []
+    for _ in range(case["boxes"]):
+        a, b = (round(_log(rng, case["nx"], case["ny"])) for _ in range(2))
+        out.append((a, b, max(1, round(_log(rng, case["ppc"] / 4.0, case["ppc"] * 4.0)))))
+    return out
+
+
 def _batch(case, g):
-    """Independent gyration boxes, sides log-uniform in [nx, ny], particles per
-    cell log-uniform in [ppc/4, 4 ppc], all in one context."""
+    """Independent gyration boxes in one context (_batch_shapes)."""
     nb = case["boxes"]
-    lo, hi = math.log(case["nx"]), math.log(case["ny"])
-    sides = (lo + (hi - lo) * _uniform(g, 2, nb)).exp().round().to(torch.int64)
-    ppc = (case["ppc"] * 4.0 ** (2.0 * _uniform(g, nb) - 1.0)).round().clamp_min(1).to(torch.int64)
+    shapes = torch.tensor(_batch_shapes(case), device=DEV).T
+    sides, ppc = shapes[:2], shapes[2]
     cells = sides[0] * sides[1]
     counts = cells * ppc
     sx, sy = (s.tolist() for s in sides)
@@ -374,11 +384,9 @@ def run(s):
 def work(case):
     nd, fp64 = case["ndim"], case["precision"] == "fp64"
     if case["pop"] == "batch":
-        # means of the log-uniform draws
-        a, b = case["nx"], case["ny"]
-        side = (b - a) / math.log(b / a) if b > a else a
-        nc = case["boxes"] * side * side
-        N = nc * case["ppc"] * (16.0 - 1.0) / 4.0 / math.log(16.0)
+        shapes = _batch_shapes(case)
+        nc = sum(a * b for a, b, _ in shapes)
+        N = sum(a * b * p for a, b, p in shapes)
     else:
         nc = case["nx"] * case["ny"] * case["nz"]
         N = max(1, round(nc * case["ppc"]))
