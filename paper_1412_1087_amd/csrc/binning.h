@@ -227,11 +227,12 @@ k_bin_offsets(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ ite
     }
     const uint32_t c = run - s0;
     const uint32_t io = item_first_next[d];
-    for (uint32_t q = (uint32_t)lane; q * (uint32_t)P < c; q += 64) {
+    const uint32_t ni = (c + (uint32_t)P - 1) / (uint32_t)P;  // of even size
+    for (uint32_t q = (uint32_t)lane; q < ni; q += 64) {
         WorkItem w;
         w.tile = d;
-        w.begin = (int32_t)(s0 + q * (uint32_t)P);
-        w.end = (int32_t)(s0 + min((q + 1) * (uint32_t)P, c));
+        w.begin = (int32_t)(s0 + (uint32_t)((uint64_t)c * q / ni));
+        w.end = (int32_t)(s0 + (uint32_t)((uint64_t)c * (q + 1) / ni));
         w.box = tile_box[d];
         items_next[io + q] = w;
     }
@@ -530,8 +531,8 @@ __global__ void k_key_cell(PS P, uint32_t* __restrict__ key, uint32_t* __restric
 }
 
 // The same sort with per-block tile histograms in LDS, for a tile count that
-// fits (NT <= kSortLdsTiles): each block takes kSortChunk consecutive
-// particles, counts their tiles in LDS and adds each non-zero count to the
+// fits (NT <= kSortLdsTiles): each block takes `chunk` (at most kSortChunk)
+// consecutive particles, counts their tiles in LDS and adds each non-zero count to the
 // global counter once, so a counter sees one atomic per block however the
 // particles are ordered.
 constexpr int kSortChunk = 4096;
@@ -540,16 +541,16 @@ constexpr int kSortLdsTiles = 32768;  // 128 KB of LDS histogram at most
 template <int NDIM, typename PS>
 __global__ void __launch_bounds__(256)
 k_key_count_lds(PS P, uint32_t* __restrict__ key, uint32_t* __restrict__ count,
-                const BoxDev* __restrict__ boxes, SlotBoxes sb, int64_t N, int NT) {
+                const BoxDev* __restrict__ boxes, SlotBoxes sb, int64_t N, int NT, int chunk) {
     extern __shared__ uint32_t s_h[];
     constexpr int U = kSortChunk / 256;
     for (int t = threadIdx.x; t < NT; t += 256) s_h[t] = 0;
     __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * kSortChunk;
+    const int64_t j0 = (int64_t)blockIdx.x * chunk, j1 = min(j0 + chunk, N);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t j = j0 + threadIdx.x + u * 256;
-        if (j < N) {
+        if (j < j1) {
             const uint32_t k = sort_key<NDIM>(P, j, sb, boxes);
             key[j] = k;
             if (k != kNoTile) atomicAdd(&s_h[k], 1u);
@@ -567,17 +568,17 @@ k_key_count_lds(PS P, uint32_t* __restrict__ key, uint32_t* __restrict__ count,
 template <int NDIM, typename PS>
 __global__ void __launch_bounds__(256)
 k_scatter_lds(PS A, PS Bo, const uint32_t* __restrict__ key, uint32_t* __restrict__ cursor,
-              int64_t N, int NT) {
+              int64_t N, int NT, int chunk) {
     extern __shared__ uint32_t s_h[];
     constexpr int U = kSortChunk / 256;
     for (int t = threadIdx.x; t < NT; t += 256) s_h[t] = 0;
     __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * kSortChunk;
+    const int64_t j0 = (int64_t)blockIdx.x * chunk, j1 = min(j0 + chunk, N);
     uint32_t k[U], r[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t j = j0 + threadIdx.x + u * 256;
-        k[u] = j < N ? key[j] : kNoTile;
+        k[u] = j < j1 ? key[j] : kNoTile;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) r[u] = k[u] != kNoTile ? atomicAdd(&s_h[k[u]], 1u) : 0u;

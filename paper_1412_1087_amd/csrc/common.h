@@ -29,7 +29,7 @@ enum : uint32_t {
 constexpr double kMagic = 6755399441055744.0;
 constexpr uint32_t kMagicHi = 0x43380000u;
 constexpr double kMaxAmount = 2251799813685248.0;  // 2^51
-constexpr int kItemParticles = 4096;  // particles per work item (at most)
+constexpr int kItemParticles = 4096;  // particles per work item, at most (Layout::P in a context)
 
 // Box descriptor as the kernels see it.  Per-call fields (dt, hdt, hdx) are
 // refreshed by mhdpic_step before its kernels are enqueued.

@@ -296,11 +296,12 @@ k_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ start,
         start[i] = off;
         cursor[i] = off;
         item_first[i] = io;
-        for (uint32_t k = 0; k < c; k += (uint32_t)P) {
+        const uint32_t ni = (c + (uint32_t)P - 1) / (uint32_t)P;  // of even size
+        for (uint32_t k = 0; k < ni; ++k) {
             WorkItem w;
             w.tile = i;
-            w.begin = (int32_t)(base + off + k);
-            w.end = (int32_t)(base + off + min(k + (uint32_t)P, c));
+            w.begin = (int32_t)(base + off + (uint32_t)((uint64_t)c * k / ni));
+            w.end = (int32_t)(base + off + (uint32_t)((uint64_t)c * (k + 1) / ni));
             w.box = tile_box[i];
             items[io++] = w;
         }

@@ -16,6 +16,7 @@
 #include <cstring>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/mhdpic.h"
@@ -100,10 +101,31 @@ TileShape default_tile(int ndim, int64_t cells, int64_t np) {
     return {8, 4, 4};
 }
 
+// Particles per work item, at most: the largest power of two up to 4096 that
+// gives an item for each of the 256 CUs, else 512, one pass of the push's
+// block.  boxes: (tiles, particle slots) of each.  An item is one block of the
+// push and of the binning's kernels, and a block takes about 50 us for 4096
+// particles however few blocks there are: with items of 4096 a step of a 32^2
+// box (16384 particles, four blocks) took 81 us and takes 46 us with 512; a
+// 256^2 box with 8 per cell (128 tiles) 92 and 84 us.  Each item also stages
+// its tile's fields and flushes its deposits, so more items than CUs do not
+// pay: wanting 512 of them, a 32^3 box with 16 per cell (256 tiles of 2048)
+// went from 108 to 121 us a step.
+constexpr int64_t kItemsWanted = 256;
+int32_t item_particles(const std::vector<std::pair<int64_t, int64_t>>& boxes) {
+    for (int32_t P = kItemParticles; P > 512; P /= 2) {
+        int64_t items = 0;
+        for (const auto& b : boxes) items += b.first * ((b.second + b.first * P - 1) / (b.first * P));
+        if (items >= kItemsWanted) return P;
+    }
+    return 512;
+}
+
 struct Layout {
     // sizes: N particle slots (the capacity), N0 particles at initialisation
     int64_t N = 0, N0 = 0, NC = 0;
     int32_t NT = 0, NW = 0;
+    int32_t P = kItemParticles;  // particles per work item, at most
     bool tagged = false;  // particles carry tags (the context has a capacity for additions)
     // offsets into the workspace
     size_t partA = 0, partB = 0, part_bytes = 0;
@@ -251,8 +273,9 @@ int validate_boxes(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
 }
 
 Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32_t precision,
-                   int ndim, const std::vector<TileShape>& tiles) {
+                   int ndim, const std::vector<TileShape>& tiles, bool large_items = false) {
     Layout L;
+    std::vector<std::pair<int64_t, int64_t>> sizes;
     for (int b = 0; b < nb; ++b) {
         const mhdpic_box& B = boxes[b];
         L.N += std::max<int64_t>(np[b], B.capacity);
@@ -263,10 +286,12 @@ Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
         int ntx = (B.n[0] + tile.x - 1) / tile.x, nty = (B.n[1] + tile.y - 1) / tile.y;
         int ntz = ndim == 3 ? (B.n[2] + tile.z - 1) / tile.z : 1;
         L.NT += ntx * nty * ntz;
+        sizes.emplace_back((int64_t)ntx * nty * ntz, std::max<int64_t>(np[b], B.capacity));
     }
-    // work items: one per tile and one per 4096 slots, and as many again for a
+    // work items: one per tile and one per P slots, and as many again for a
     // tail of added particles in contexts with a capacity
-    L.NW = L.NT + (int32_t)(L.N / kItemParticles) + 1;
+    L.P = large_items ? kItemParticles : item_particles(sizes);
+    L.NW = L.NT + (int32_t)(L.N / L.P) + 1;
     if (L.tagged) L.NW = 2 * L.NW;
     const size_t N = (size_t)L.N, NC = (size_t)L.NC;
     const size_t fsz = precision == MHDPIC_FP64 ? 8 : 4;
@@ -420,7 +445,7 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys) {
     const unsigned gT = grid_for(L.NT, 4);  // one wave per tile, 4 waves per block
     hipLaunchKernelGGL(k_bin_count<NDIM>, dim3(gT), dim3(256), 0, s, at<uint32_t>(c, L.cnt),
                        at<uint32_t>(c, L.item_first[it]), at<int32_t>(c, L.tile_box), bd,
-                       at<uint32_t>(c, L.count), at<uint32_t>(c, L.cursor), L.NT, kItemParticles);
+                       at<uint32_t>(c, L.count), at<uint32_t>(c, L.cursor), L.NT, L.P);
     hipLaunchKernelGGL(k_scan2, dim3(1), dim3(1024), 0, s, at<uint32_t>(c, L.count),
                        at<uint32_t>(c, L.cursor), at<uint32_t>(c, L.start),
                        at<uint32_t>(c, L.item_first[1 - it]), at<uint32_t>(c, L.n_items[1 - it]), L.NT);
@@ -428,7 +453,7 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys) {
                        at<uint32_t>(c, L.item_first[it]), at<uint32_t>(c, L.off),
                        at<int32_t>(c, L.tile_box), bd, at<uint32_t>(c, L.start),
                        at<uint32_t>(c, L.item_first[1 - it]), at<WorkItem>(c, L.items[1 - it]),
-                       L.NT, kItemParticles);
+                       L.NT, L.P);
     // where the particles move (mhdpic_set_particle_moves): in the push, the
     // binning moves only the ids (and tags) and leaves the map from new slots
     // to old ones, through which the push reads the particles and writes them,
@@ -487,7 +512,11 @@ int launch_sort(mhdpic_ctx* c, hipStream_t s, int64_t n, int64_t slot0, bool tai
     // per-block LDS histograms when the tiles fit (up to 128 KB of LDS), else
     // one atomic per distinct tile in each wave
     const bool lds = L.NT <= kSortLdsTiles;
-    const unsigned gC = (unsigned)((n + kSortChunk - 1) / kSortChunk);
+    // (few particles: smaller chunks, so that they fill the chip; each block
+    // also goes over all the tiles)
+    int chunk = 256;
+    while (chunk < kSortChunk && (n > (int64_t)chunk * 1024 || chunk < L.NT)) chunk *= 2;
+    const unsigned gC = (unsigned)((n + chunk - 1) / chunk);
     const size_t hbytes = (size_t)L.NT * sizeof(uint32_t);
     if (lds && hbytes > 65536) {
         HIP_TRY(hipFuncSetAttribute((const void*)k_key_count_lds<NDIM, PS>,
@@ -498,7 +527,7 @@ int launch_sort(mhdpic_ctx* c, hipStream_t s, int64_t n, int64_t slot0, bool tai
     if (n > 0 && lds)
         hipLaunchKernelGGL((k_key_count_lds<NDIM, PS>), dim3(gC), dim3(256), hbytes, s, A,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.count), at<BoxDev>(c, L.boxes),
-                           sb, n, L.NT);
+                           sb, n, L.NT, chunk);
     else if (n > 0)
         hipLaunchKernelGGL((k_key_cell<NDIM, PS>), dim3(grid_for(n, 256)), dim3(256), 0, s, A,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.count), at<BoxDev>(c, L.boxes),
@@ -507,11 +536,11 @@ int launch_sort(mhdpic_ctx* c, hipStream_t s, int64_t n, int64_t slot0, bool tai
                        at<uint32_t>(c, tail ? L.tail_start : L.start), at<uint32_t>(c, L.cursor),
                        at<int32_t>(c, L.tile_box), at<WorkItem>(c, tail ? L.tail_items : L.items[0]),
                        at<uint32_t>(c, tail ? L.tail_first : L.item_first[0]),
-                       at<uint32_t>(c, tail ? L.tail_n : L.n_items[0]), L.NT, kItemParticles,
+                       at<uint32_t>(c, tail ? L.tail_n : L.n_items[0]), L.NT, L.P,
                        (uint32_t)slot0);
     if (n > 0 && lds)
         hipLaunchKernelGGL((k_scatter_lds<NDIM, PS>), dim3(gC), dim3(256), hbytes, s, A, Bo,
-                           at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n, L.NT);
+                           at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n, L.NT, chunk);
     else if (n > 0)
         hipLaunchKernelGGL((k_scatter<NDIM, PS>), dim3(grid_for(n, 256)), dim3(256), 0, s, A, Bo,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n);
@@ -946,6 +975,9 @@ int open_context(mhdpic_ctx* c, const mhdpic_box* boxes, int32_t n_boxes, const 
     Layout L = make_layout(boxes, n_boxes, np, precision, ndim, tiles);
     if (!workspace) return fail(MHDPIC_EINVAL, "workspace is NULL");
     if (((uintptr_t)workspace) % kAlign) return fail(MHDPIC_EINVAL, "workspace must be 256-byte aligned");
+    // (smaller items take some more workspace: a workspace that only holds the
+    // layout with the largest ones gets that)
+    if (ws_bytes < L.total) L = make_layout(boxes, n_boxes, np, precision, ndim, tiles, true);
     if (ws_bytes < L.total) return fail(MHDPIC_ENOMEM, "workspace too small");
     if (L.N0 > 0 && (!x || !v || !m || !qm)) return fail(MHDPIC_EINVAL, "particle arrays are NULL");
     c->ndim = ndim;
@@ -1274,7 +1306,7 @@ int mhdpic_advance_noalloc(const mhdpic_box* boxes, int32_t n_boxes, const int64
     std::vector<TileShape> tiles;
     int rc = validate_boxes(boxes, n_boxes, n_particles, precision, ndim, tiles);
     if (rc) return rc;
-    const size_t need = make_layout(boxes, n_boxes, n_particles, precision, ndim, tiles).total;
+    const size_t need = make_layout(boxes, n_boxes, n_particles, precision, ndim, tiles, true).total;
     if (need > kScratchBytes) {
         std::snprintf(g_last_error, sizeof(g_last_error),
                       "mhdpic_advance_noalloc: these boxes and particles need %zu bytes of scratch; "
@@ -1735,7 +1767,7 @@ int mhdpic_inject(mhdpic_ctx* c, const int64_t* n_new, const double* x, const do
         HIP_TRY(hipMemcpyAsync(&used[1], c->ws + L.n_items[c->it], 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         const int64_t s0 = (int64_t)used[0] + c->tail;
-        const int64_t items_max = (int64_t)used[1] + std::min<int64_t>(L.NT, total) + total / kItemParticles + 1;
+        const int64_t items_max = (int64_t)used[1] + std::min<int64_t>(L.NT, total) + total / L.P + 1;
         if (s0 + total <= L.N && items_max <= L.NW) break;
         if (pass == 1)
             return fail(MHDPIC_ENOMEM, "the context's particle slots (the boxes' capacity) are full");
