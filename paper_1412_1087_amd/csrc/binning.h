@@ -108,133 +108,185 @@ struct TileGroups {
             i0 = item_first[s];
             n = item_first[s + 1] - i0;
         }
-        uint32_t x = n;  // inclusive scan over the lanes
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o);
-            if (lane >= o) x += y;
-        }
+        const uint32_t x = wave_scan(n);
         pre = x - n;
         total = __shfl(x, 63);
     }
-    // code and item of group g (g < total); every lane of the wave calls it
+    // code and item of group g (g < total): the last code with pre <= g; every
+    // lane of the wave calls it
     __device__ __forceinline__ void group(uint32_t g, int& k, uint32_t& item) const {
         k = 0;
-        for (int q = 1; q < K; ++q)
-            if ((uint32_t)__shfl(pre, q) <= g) k = q;
-        item = (uint32_t)__shfl(i0, k) + (g - (uint32_t)__shfl(pre, k));
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) {
+            const uint32_t p = (uint32_t)__shfl((int)pre, min(k + o, K - 1));
+            if (k + o < K && p <= g) k += o;
+        }
+        item = (uint32_t)__shfl((int)i0, k) + (g - (uint32_t)__shfl((int)pre, k));
     }
 };
 
-// Per destination tile: particles arriving from the (item, code) groups of
-// the current work list, and the number of next-step work items.  One wave
-// per tile.
-template <int NDIM>
-__global__ void __launch_bounds__(256)
-k_bin_count(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_first,
-            const int32_t* __restrict__ tile_box, const BoxDev* __restrict__ boxes,
-            uint32_t* __restrict__ tile_count, uint32_t* __restrict__ tile_items, int NT, int P) {
-    constexpr int K = Codes<NDIM>::K;
-    const int lane = threadIdx.x & 63;
-    const int d = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (d >= NT) return;  // whole wave
-    TileGroups<NDIM> tg;
-    tg.load(boxes[tile_box[d]], d, item_first, lane);
-    uint32_t tot = 0;
-    for (uint32_t g0 = 0; g0 < tg.total; g0 += 64) {  // the same trip count in every lane
-        int k;
-        uint32_t i;
-        tg.group(g0 + lane, k, i);
-        if (g0 + lane < tg.total) tot += cnt[(size_t)i * K + k];
-    }
-    for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o);
-    if (lane == 0) {
-        tile_count[d] = tot;
-        tile_items[d] = (tot + (uint32_t)P - 1) / (uint32_t)P;
-    }
+constexpr int kPlanBlock = 1024;  // threads: one wave per tile
+
+// Share of the blocks of k_bin_plan: `ticket` counts the blocks that ever
+// began (so its quotient by a launch's blocks numbers the launch), and word b
+// of `state` is what block b has published, of a launch's parity (bit 63): its
+// own sums (bit 62 clear), later the sums up to and including it (bit 62 set),
+// slots in bits 0-30 and items in bits 31-61.  Every launch over a context has
+// the same blocks and leaves every word with its parity, so nothing is cleared
+// between launches; at set-up all words are zero and the first parity is 1.
+struct PlanShare {
+    unsigned long long* ticket;
+    unsigned long long* state;
+};
+
+__device__ __forceinline__ unsigned long long plan_word(uint32_t par, bool all, uint32_t slots,
+                                                        uint32_t items) {
+    return (unsigned long long)par << 63 | (unsigned long long)all << 62 |
+           (unsigned long long)items << 31 | slots;
 }
 
-// One block: exclusive scans of tile_count (-> start) and tile_items
-// (-> item_first_next, with the total in n_items_next).
-__global__ void __launch_bounds__(1024)
-k_scan2(const uint32_t* __restrict__ tile_count, const uint32_t* __restrict__ tile_items,
-        uint32_t* __restrict__ start, uint32_t* __restrict__ item_first_next,
-        uint32_t* __restrict__ n_items_next, int NT) {
-    __shared__ uint32_t s_a[1024], s_b[1024];
-    const int t = threadIdx.x;
-    const int per = (NT + 1023) / 1024;
-    const int t0 = min(t * per, NT), t1 = min(t0 + per, NT);
-    uint32_t sa = 0, sb = 0;
-    for (int i = t0; i < t1; ++i) {
-        sa += tile_count[i];
-        sb += tile_items[i];
+// Sums of the blocks before block t (exclusive), and the publication of its
+// own: the block publishes its sums a, b, then reads backwards, 64 words at a
+// time, until a block that knows all sums before it.  One whole wave calls it.
+// Every wait ends: tickets are given out as blocks begin, a block publishes
+// before it waits, and it waits for smaller tickets only.
+__device__ __forceinline__ void plan_prefix(const PlanShare& ps, uint32_t t, uint32_t par, uint32_t a,
+                                            uint32_t b, uint32_t& sa, uint32_t& sb) {
+    const int lane = lane_id();
+    sa = sb = 0;
+    if (lane == 0)
+        __hip_atomic_store(&ps.state[t], plan_word(par, t == 0, a, b), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    for (int64_t p = (int64_t)t - 1; p >= 0; p -= 64) {
+        const bool in = p - lane >= 0;
+        unsigned long long w;
+        uint64_t full;  // lanes whose block knows all sums before it
+        for (;;) {
+            w = in ? __hip_atomic_load(&ps.state[p - lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+            const bool here = in && (uint32_t)(w >> 63) == par;
+            const uint64_t got = __ballot(here || !in);
+            full = __ballot(here && (w >> 62 & 1ull));
+            // enough: every word up to the nearest full one (or all 64)
+            const uint64_t need = full ? (full & (0ull - full)) * 2ull - 1ull : ~0ull;
+            if ((got & need) == need) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        const int last = full ? __ffsll((unsigned long long)full) - 1 : 63;
+        const bool add = in && lane <= last;
+        uint32_t xa = add ? (uint32_t)w & 0x7FFFFFFFu : 0u, xb = add ? (uint32_t)(w >> 31) & 0x7FFFFFFFu : 0u;
+        for (int o = 32; o > 0; o >>= 1) {
+            xa += (uint32_t)__shfl_xor((int)xa, o);
+            xb += (uint32_t)__shfl_xor((int)xb, o);
+        }
+        sa += xa;
+        sb += xb;
+        if (full) break;
     }
-    s_a[t] = sa;
-    s_b[t] = sb;
+    if (lane == 0 && t > 0)
+        __hip_atomic_store(&ps.state[t], plan_word(par, true, sa + a, sb + b), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The plan of a binning, from the counts of every (item, code) group: slots
+// and work items for each destination tile, both in tile order, and the offset
+// of each arriving group (in the order of TileGroups), with the totals in
+// *used and *n_items_next.  One wave per tile; the blocks add up their tiles
+// and find the sums before them as they go (plan_prefix).  Bound by the
+// latency of its few dependent loads: one launch of 10 us in place of a count,
+// a scan of all tiles in one block and the offsets (a binning of the 64^3 box,
+// 2048 tiles, went from 39 to 33 us, of the 128^3 one, 32768 tiles, from 409 to
+// 315, and a step of a 32^2 box from 47 to 40).  (Slots given out in the order in
+// which the blocks come would save the prefix, but the push then runs
+// neighbouring tiles, whose particles share lines of memory, far apart in time
+// and on other XCDs: on the shock strip it went from 140 to 180 us.)
+template <int NDIM>
+__global__ void __launch_bounds__(kPlanBlock)
+k_bin_plan(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_first,
+           uint32_t* __restrict__ off, const int32_t* __restrict__ tile_box,
+           const BoxDev* __restrict__ boxes, uint32_t* __restrict__ item_first_next,
+           WorkItem* __restrict__ items_next, uint32_t* __restrict__ n_items_next,
+           uint32_t* __restrict__ used, PlanShare ps, int NT, int P) {
+    constexpr int K = Codes<NDIM>::K;
+    constexpr int NWV = kPlanBlock / 64;
+    __shared__ uint32_t s_slots[NWV], s_items[NWV], s_t, s_par;
+    const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+    if (threadIdx.x == 0) {
+        const unsigned long long n = atomicAdd(ps.ticket, 1ull);
+        s_t = (uint32_t)(n % gridDim.x);
+        s_par = (uint32_t)(n / gridDim.x + 1ull) & 1u;
+    }
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        uint32_t a = t >= o ? s_a[t - o] : 0u;
-        uint32_t b = t >= o ? s_b[t - o] : 0u;
-        __syncthreads();
-        s_a[t] += a;
-        s_b[t] += b;
-        __syncthreads();
-    }
-    uint32_t ra = s_a[t] - sa, rb = s_b[t] - sb;
-    for (int i = t0; i < t1; ++i) {
-        start[i] = ra;
-        item_first_next[i] = rb;
-        ra += tile_count[i];
-        rb += tile_items[i];
-    }
-    if (t == 1023) {
-        start[NT] = s_a[1023];
-        item_first_next[NT] = s_b[1023];
-        *n_items_next = s_b[1023];
-    }
-}
-
-// Per destination tile: the offset of every arriving (item, code) group, in
-// the order of TileGroups, and the tile's next-step work items.  One wave per
-// tile; group counts are scanned across the wave.
-template <int NDIM>
-__global__ void __launch_bounds__(256)
-k_bin_offsets(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_first,
-              uint32_t* __restrict__ off, const int32_t* __restrict__ tile_box,
-              const BoxDev* __restrict__ boxes, const uint32_t* __restrict__ start,
-              const uint32_t* __restrict__ item_first_next,
-              WorkItem* __restrict__ items_next, int NT, int P) {
-    constexpr int K = Codes<NDIM>::K;
-    const int lane = threadIdx.x & 63;
-    const int d = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (d >= NT) return;  // whole wave
+    const uint32_t t = s_t;
+    const int d = (int)t * NWV + wave;           // this wave's tile
+    const bool has = d < NT;                     // (whole wave)
     TileGroups<NDIM> tg;
-    tg.load(boxes[tile_box[d]], d, item_first, lane);
-    const uint32_t s0 = start[d];
+    uint32_t c0 = 0, to0 = 0;  // the lane's first group: its particles, its offset's place
+    uint32_t tot = 0;
+    int32_t box = 0;
+    if (has) {
+        box = tile_box[d];
+        tg.load(boxes[box], d, item_first, lane);
+        for (uint32_t g0 = 0; g0 < tg.total; g0 += 64) {  // the same trip count in every lane
+            int k;
+            uint32_t i;
+            tg.group(g0 + lane, k, i);
+            const uint32_t to = i * K + (uint32_t)k;
+            const uint32_t c = g0 + lane < tg.total ? cnt[to] : 0u;
+            if (g0 == 0) {
+                c0 = c;
+                to0 = to;
+            }
+            tot += c;
+        }
+        for (int o = 32; o > 0; o >>= 1) tot += (uint32_t)__shfl_xor((int)tot, o);
+    }
+    const uint32_t ni = (tot + (uint32_t)P - 1) / (uint32_t)P;  // items of even size
+    if (lane == 0) {
+        s_slots[wave] = tot;
+        s_items[wave] = ni;
+    }
+    __syncthreads();
+    if (wave == 0) {  // scan over the block's tiles
+        const uint32_t a = lane < NWV ? s_slots[lane] : 0u, b = lane < NWV ? s_items[lane] : 0u;
+        const uint32_t x = wave_scan(a), y = wave_scan(b);
+        const uint32_t ta = (uint32_t)__shfl((int)x, 63), tb = (uint32_t)__shfl((int)y, 63);
+        uint32_t sb, ib;
+        plan_prefix(ps, t, s_par, ta, tb, sb, ib);
+        if (lane == 0 && t == gridDim.x - 1u) {
+            *used = sb + ta;
+            *n_items_next = ib + tb;
+            item_first_next[NT] = ib + tb;
+        }
+        if (lane < NWV) {
+            s_slots[lane] = sb + x - a;
+            s_items[lane] = ib + y - b;
+        }
+    }
+    __syncthreads();
+    if (!has) return;
+    const uint32_t s0 = s_slots[wave], io = s_items[wave];
     uint32_t run = s0;
     for (uint32_t g0 = 0; g0 < tg.total; g0 += 64) {  // the same trip count in every lane
-        int k;
-        uint32_t i;
-        tg.group(g0 + lane, k, i);
-        const bool in = g0 + lane < tg.total;
-        const uint32_t c = in ? cnt[(size_t)i * K + k] : 0u;
-        uint32_t x = c;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o);
-            if (lane >= o) x += y;
+        uint32_t c = c0, to = to0;
+        if (g0 > 0) {
+            int k;
+            uint32_t i;
+            tg.group(g0 + lane, k, i);
+            to = i * K + (uint32_t)k;
+            c = g0 + lane < tg.total ? cnt[to] : 0u;
         }
-        if (in) off[(size_t)i * K + k] = run + x - c;
-        run += __shfl(x, 63);
+        const uint32_t x = wave_scan(c);
+        if (g0 + lane < tg.total) off[to] = run + x - c;
+        run += (uint32_t)__shfl((int)x, 63);
     }
-    const uint32_t c = run - s0;
-    const uint32_t io = item_first_next[d];
-    const uint32_t ni = (c + (uint32_t)P - 1) / (uint32_t)P;  // of even size
-    for (uint32_t q = (uint32_t)lane; q < ni; q += 64) {
+    if (lane == 0) item_first_next[d] = io;
+    for (uint32_t k = (uint32_t)lane; k < ni; k += 64) {
         WorkItem w;
         w.tile = d;
-        w.begin = (int32_t)(s0 + (uint32_t)((uint64_t)c * q / ni));
-        w.end = (int32_t)(s0 + (uint32_t)((uint64_t)c * (q + 1) / ni));
-        w.box = tile_box[d];
-        items_next[io + q] = w;
+        w.begin = (int32_t)(s0 + (uint32_t)((uint64_t)tot * k / ni));
+        w.end = (int32_t)(s0 + (uint32_t)((uint64_t)tot * (k + 1) / ni));
+        w.box = box;
+        items_next[io + k] = w;
     }
 }
 
@@ -325,11 +377,30 @@ constexpr int kMapChunk2D = MHDPIC_MAP_CHUNK_2D;
 // which brings it to about 10 lines for a few more same-residue lanes.  The
 // particles of the 3D boxes (drifting beams) keep their order from step to
 // step well enough, and there the stay classes pay for themselves.
+//
+// nfield blocks of the grid prepare the cell-centred fields of the step that
+// the binning begins (fieldprep_cell), in groups of eight spread evenly over
+// the items' blocks: ranking in LDS and streaming the fields then overlap (a
+// shock box of 8192 x 256 cells: 72 us together, 29 and 57 apart), and a small
+// step is one launch shorter.  In the plan's launch instead, whose few waves
+// wait on one load after another, the plan took as long as the streaming made
+// its loads wait: 84 us there.
 template <int NDIM, typename PS, int BLOCK, bool TAGGED, bool MAP>
 __global__ void __launch_bounds__(BLOCK)
 k_bin_scatter_class(PS A, PS Bo, const uint16_t* __restrict__ code, const uint32_t* __restrict__ off,
                     const WorkItem* __restrict__ items, const uint32_t* __restrict__ n_items,
-                    uint32_t* __restrict__ map) {
+                    uint32_t* __restrict__ map, const BoxDev* __restrict__ boxes,
+                    FieldArgs<typename PS::R> fa, uint32_t nfield) {
+    uint32_t bid = blockIdx.x;
+    if (nfield) {
+        const uint32_t g = bid >> 3, ng = gridDim.x >> 3, nf = nfield >> 3;
+        const uint32_t f0 = (uint32_t)((uint64_t)g * nf / ng), f1 = (uint32_t)((uint64_t)(g + 1) * nf / ng);
+        if (f1 > f0) {
+            fieldprep_cell(fa, boxes, (int64_t)(f0 * 8 + (bid & 7u)) * BLOCK + threadIdx.x);
+            return;
+        }
+        bid -= f0 * 8;
+    }
     constexpr int K = Codes<NDIM>::K;
     constexpr int STAY = Codes<NDIM>::STAY;
     constexpr int NCL = K;        // shift classes (3^NDIM)
@@ -350,7 +421,7 @@ k_bin_scatter_class(PS A, PS Bo, const uint16_t* __restrict__ code, const uint32
     __shared__ SR s_stage[kItemParticles];
     uint32_t* s_key = reinterpret_cast<uint32_t*>(s_stage);  // ranks, until the moves
     uint32_t item;
-    if (!item_of_block(n_items, item)) return;
+    if (!item_of_block(n_items, item, bid)) return;
     const WorkItem w = items[item];
     if (w.end - w.begin > kItemParticles) return;  // never built larger
     using R = typename PS::R;

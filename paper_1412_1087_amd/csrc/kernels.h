@@ -44,6 +44,16 @@ __device__ __forceinline__ uint32_t wave_claim(uint32_t* counters, uint32_t key,
     return slot;
 }
 
+// Inclusive scan over the lanes of a wave (every lane calls it).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+    const int lane = lane_id();
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)x, o);
+        if (lane >= o) x += y;
+    }
+    return x;
+}
+
 __device__ __forceinline__ int pmod(int a, int n) {
     int r = a % n;
     return r < 0 ? r + n : r;
@@ -262,12 +272,12 @@ struct SlotBoxes {
 
 // Exclusive scan of tile counts and the work list: each tile's particles are
 // split into items of at most P particles; items name slots from base on.
-// One block of 1024 threads.
+// *total receives the particles.  One block of 1024 threads.
 __global__ void __launch_bounds__(1024)
-k_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ start,
-       uint32_t* __restrict__ cursor, const int32_t* __restrict__ tile_box,
-       WorkItem* __restrict__ items, uint32_t* __restrict__ item_first,
-       uint32_t* __restrict__ n_items, int NT, int P, uint32_t base) {
+k_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ cursor,
+       const int32_t* __restrict__ tile_box, WorkItem* __restrict__ items,
+       uint32_t* __restrict__ item_first, uint32_t* __restrict__ n_items,
+       uint32_t* __restrict__ total, int NT, int P, uint32_t base) {
     __shared__ uint32_t s_a[1024], s_b[1024];
     const int t = threadIdx.x;
     const int per = (NT + 1023) / 1024;
@@ -293,7 +303,6 @@ k_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ start,
     uint32_t io = s_b[t] - nit;
     for (int i = t0; i < t1; ++i) {
         uint32_t c = count[i];
-        start[i] = off;
         cursor[i] = off;
         item_first[i] = io;
         const uint32_t ni = (c + (uint32_t)P - 1) / (uint32_t)P;  // of even size
@@ -308,7 +317,7 @@ k_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ start,
         off += c;
     }
     if (t == 1023) {
-        start[NT] = s_a[1023];
+        *total = s_a[1023];
         item_first[NT] = s_b[1023];
         *n_items = s_b[1023];
     }
@@ -469,14 +478,16 @@ __device__ __forceinline__ int next_code(const BoxDev& bx, int3 T, int tx, int t
     return k;
 }
 
-__device__ __forceinline__ bool item_of_block(const uint32_t* n_items, uint32_t& item) {
+__device__ __forceinline__ bool item_of_block(const uint32_t* n_items, uint32_t& item, uint32_t bid) {
     const uint32_t nitems = *n_items;
     const uint32_t per_xcd = (nitems + 7u) / 8u;
-    const uint32_t bid = blockIdx.x;
     const uint32_t slot = bid >> 3;
     if (slot >= per_xcd) return false;
     item = (bid & 7u) * per_xcd + slot;
     return item < nitems;
+}
+__device__ __forceinline__ bool item_of_block(const uint32_t* n_items, uint32_t& item) {
+    return item_of_block(n_items, item, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -486,14 +497,25 @@ __device__ __forceinline__ bool item_of_block(const uint32_t* n_items, uint32_t&
 // Writes EB[cell] = (Ex, Ey, Ez, Bx, By, Bz) interleaved for the gather, and
 // clears the cell's n_CR, J_CR in nJ_next, which the push then fills.
 template <typename TF>
-__global__ void k_fieldprep(TF* __restrict__ EB, const double* __restrict__ B,
-                            const double* __restrict__ vg, const double* __restrict__ rho,
-                            const int64_t* __restrict__ nJ, int64_t* __restrict__ nJ_next,
-                            const BoxDev* __restrict__ boxes,
-                            const int64_t* __restrict__ cell_off, int nb, int64_t NC) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+struct FieldArgs {
+    TF* EB;
+    const double *B, *vg, *rho;
+    const int64_t* nJ;
+    int64_t* nJ_next;
+    const int64_t* cell_off;
+    int nb;
+    int64_t NC;
+};
+
+template <typename TF>
+__device__ __forceinline__ void fieldprep_cell(const FieldArgs<TF>& fa, const BoxDev* boxes, int64_t c) {
+    const int64_t NC = fa.NC;
     if (c >= NC) return;
-    const BoxDev& bx = boxes[find_box(cell_off, nb, c)];
+    const double* __restrict__ B = fa.B;
+    const double* __restrict__ vg = fa.vg;
+    const double* __restrict__ rho = fa.rho;
+    const int64_t* __restrict__ nJ = fa.nJ;
+    const BoxDev& bx = boxes[find_box(fa.cell_off, fa.nb, c)];
     double b0 = B[c], b1 = B[NC + c], b2 = B[2 * NC + c];
     double g0 = vg[c], g1 = vg[NC + c], g2 = vg[2 * NC + c];
     double e0[3];
@@ -517,7 +539,7 @@ __global__ void k_fieldprep(TF* __restrict__ EB, const double* __restrict__ B,
             e[d] = e0[d] - F / ng;
         }
     }
-    TF* o = EB + 6 * c;
+    TF* __restrict__ o = fa.EB + 6 * c;
     o[0] = (TF)e[0];
     o[1] = (TF)e[1];
     o[2] = (TF)e[2];
@@ -525,7 +547,14 @@ __global__ void k_fieldprep(TF* __restrict__ EB, const double* __restrict__ B,
     o[4] = (TF)b1;
     o[5] = (TF)b2;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) nJ_next[q * NC + c] = 0;
+    for (int q = 0; q < 4; ++q) fa.nJ_next[q * NC + c] = 0;
+}
+
+// The fields in a launch of their own (a timed step).
+template <typename TF>
+__global__ void __launch_bounds__(256)
+k_fieldprep(FieldArgs<TF> fa, const BoxDev* __restrict__ boxes) {
+    fieldprep_cell(fa, boxes, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // Cell-centred feedback of the predictor step (App. A.3), in code units

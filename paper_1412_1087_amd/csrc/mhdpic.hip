@@ -121,6 +121,9 @@ int32_t item_particles(const std::vector<std::pair<int64_t, int64_t>>& boxes) {
     return 512;
 }
 
+// Blocks of k_bin_plan over NT tiles.
+int32_t plan_blocks(int32_t NT) { return (NT + kPlanBlock / 64 - 1) / (kPlanBlock / 64); }
+
 struct Layout {
     // sizes: N particle slots (the capacity), N0 particles at initialisation
     int64_t N = 0, N0 = 0, NC = 0;
@@ -130,13 +133,15 @@ struct Layout {
     // offsets into the workspace
     size_t partA = 0, partB = 0, part_bytes = 0;
     size_t key = 0, code = 0, EB = 0, Dcorr = 0, nJ0 = 0, nJ1 = 0;
-    size_t count = 0, start = 0, cursor = 0, tile_box = 0, err = 0;
+    size_t count = 0, cursor = 0, tile_box = 0, err = 0;
     size_t items[2] = {0, 0}, n_items[2] = {0, 0}, item_first[2] = {0, 0};
+    size_t used = 0;            // slots the last sort or binning filled
+    size_t plan = 0;            // PlanShare: the ticket, then a word per block
     size_t cnt = 0, off = 0;
     int K = 27;
     size_t boxes = 0, part_off = 0, cell_off = 0, box_count = 0, n_out = 0;
-    // a sorted tail of added particles: its tile starts and work list
-    size_t tail_start = 0, tail_items = 0, tail_first = 0, tail_n = 0;
+    // the work list of a sorted tail of added particles, and its particles
+    size_t tail_items = 0, tail_first = 0, tail_n = 0, tail_used = 0;
     size_t total = 0;
 };
 
@@ -314,7 +319,6 @@ Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
     L.nJ0 = take(NC * 4 * 8);
     L.nJ1 = take(NC * 4 * 8);
     L.count = take((size_t)L.NT * 4);
-    L.start = take((size_t)(L.NT + 1) * 4);
     L.cursor = take((size_t)L.NT * 4);
     L.tile_box = take((size_t)L.NT * 4);
     for (int q = 0; q < 2; ++q) {
@@ -324,16 +328,18 @@ Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
     }
     L.cnt = take((size_t)L.NW * L.K * 4);
     L.off = take((size_t)L.NW * L.K * 4);
-    L.err = take(4);
+    L.plan = take(8 + 8 * (size_t)plan_blocks(L.NT) + 4 + 4);
+    L.err = L.plan + 8 + 8 * (size_t)plan_blocks(L.NT);
+    L.used = L.err + 4;
     L.boxes = take((size_t)nb * sizeof(BoxDev));
     L.part_off = take((size_t)(nb + 1) * 8);
     L.cell_off = take((size_t)(nb + 1) * 8);
     L.box_count = take((size_t)nb * 8);
     L.n_out = take(4);
-    L.tail_start = take((size_t)(L.NT + 1) * 4);
     L.tail_items = take((size_t)L.NW * sizeof(WorkItem));
     L.tail_first = take((size_t)(L.NT + 1) * 4);
-    L.tail_n = take(4);
+    L.tail_n = take(8);
+    L.tail_used = L.tail_n + 4;
     L.total = o;
     return L;
 }
@@ -425,9 +431,31 @@ enum BinKeys {
     kKeysStay = 2,    // none moves: a compaction that drops empty slots
 };
 
-// Re-bins the particles of the current buffer into the other one.
+// The gas fields of a step.
+struct StepFields {
+    const double *B, *vg, *rho;
+};
+
+template <typename T>
+FieldArgs<T> field_args(mhdpic_ctx* c, const StepFields& f) {
+    const Layout& L = c->L;
+    FieldArgs<T> fa;
+    fa.EB = at<T>(c, L.EB);
+    fa.B = f.B;
+    fa.vg = f.vg;
+    fa.rho = f.rho;
+    fa.nJ = at<int64_t>(c, c->nj == 0 ? L.nJ0 : L.nJ1);
+    fa.nJ_next = at<int64_t>(c, c->nj == 0 ? L.nJ1 : L.nJ0);
+    fa.cell_off = at<int64_t>(c, L.cell_off);
+    fa.nb = c->nb;
+    fa.NC = L.NC;
+    return fa;
+}
+
+// Re-bins the particles of the current buffer into the other one, and
+// prepares the fields of the step that begins with it, if given.
 template <int NDIM, typename PS, typename T>
-int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys) {
+int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fields) {
     const Layout& L = c->L;
     PS A = part<PS, T>(c, c->cur);
     PS Bo = part<PS, T>(c, 1 - c->cur);
@@ -442,17 +470,12 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys) {
         hipLaunchKernelGGL((k_stay_items<PS, NDIM>), dim3(item_grid(L)), dim3(256), 0, s, A,
                            at<uint16_t>(c, L.code), at<uint32_t>(c, L.cnt), at<WorkItem>(c, L.items[it]),
                            at<uint32_t>(c, L.n_items[it]));
-    const unsigned gT = grid_for(L.NT, 4);  // one wave per tile, 4 waves per block
-    hipLaunchKernelGGL(k_bin_count<NDIM>, dim3(gT), dim3(256), 0, s, at<uint32_t>(c, L.cnt),
-                       at<uint32_t>(c, L.item_first[it]), at<int32_t>(c, L.tile_box), bd,
-                       at<uint32_t>(c, L.count), at<uint32_t>(c, L.cursor), L.NT, L.P);
-    hipLaunchKernelGGL(k_scan2, dim3(1), dim3(1024), 0, s, at<uint32_t>(c, L.count),
-                       at<uint32_t>(c, L.cursor), at<uint32_t>(c, L.start),
-                       at<uint32_t>(c, L.item_first[1 - it]), at<uint32_t>(c, L.n_items[1 - it]), L.NT);
-    hipLaunchKernelGGL(k_bin_offsets<NDIM>, dim3(gT), dim3(256), 0, s, at<uint32_t>(c, L.cnt),
-                       at<uint32_t>(c, L.item_first[it]), at<uint32_t>(c, L.off),
-                       at<int32_t>(c, L.tile_box), bd, at<uint32_t>(c, L.start),
+    hipLaunchKernelGGL(k_bin_plan<NDIM>, dim3(plan_blocks(L.NT)), dim3(kPlanBlock), 0, s,
+                       at<uint32_t>(c, L.cnt), at<uint32_t>(c, L.item_first[it]),
+                       at<uint32_t>(c, L.off), at<int32_t>(c, L.tile_box), bd,
                        at<uint32_t>(c, L.item_first[1 - it]), at<WorkItem>(c, L.items[1 - it]),
+                       at<uint32_t>(c, L.n_items[1 - it]), at<uint32_t>(c, L.used),
+                       PlanShare{at<unsigned long long>(c, L.plan), at<unsigned long long>(c, L.plan + 8)},
                        L.NT, L.P);
     // where the particles move (mhdpic_set_particle_moves): in the push, the
     // binning moves only the ids (and tags) and leaves the map from new slots
@@ -466,9 +489,13 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys) {
                                 : k_bin_scatter_class<NDIM, PS, 256, true, false>)
                          : (map ? k_bin_scatter_class<NDIM, PS, BM, false, true>
                                 : k_bin_scatter_class<NDIM, PS, 256, false, false>);
-    hipLaunchKernelGGL(kern, dim3(item_grid(L)), dim3(map ? BM : 256), 0, s, A, Bo, at<uint16_t>(c, L.code),
-                       at<uint32_t>(c, L.off), at<WorkItem>(c, L.items[it]),
-                       at<uint32_t>(c, L.n_items[it]), at<uint32_t>(c, L.key));
+    const int block = map ? BM : 256;
+    // (whole groups of eight blocks, so that the items keep their XCDs)
+    const unsigned nfield = fields ? (grid_for(L.NC, block) + 7) / 8 * 8 : 0;
+    hipLaunchKernelGGL(kern, dim3(item_grid(L) + nfield), dim3(block), 0, s, A, Bo,
+                       at<uint16_t>(c, L.code), at<uint32_t>(c, L.off), at<WorkItem>(c, L.items[it]),
+                       at<uint32_t>(c, L.n_items[it]), at<uint32_t>(c, L.key), bd,
+                       fields ? field_args<T>(c, *fields) : FieldArgs<T>{}, nfield);
     if (map)
         c->map_pending = true;
     else
@@ -533,11 +560,11 @@ int launch_sort(mhdpic_ctx* c, hipStream_t s, int64_t n, int64_t slot0, bool tai
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.count), at<BoxDev>(c, L.boxes),
                            sb, n);
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, at<uint32_t>(c, L.count),
-                       at<uint32_t>(c, tail ? L.tail_start : L.start), at<uint32_t>(c, L.cursor),
-                       at<int32_t>(c, L.tile_box), at<WorkItem>(c, tail ? L.tail_items : L.items[0]),
+                       at<uint32_t>(c, L.cursor), at<int32_t>(c, L.tile_box),
+                       at<WorkItem>(c, tail ? L.tail_items : L.items[0]),
                        at<uint32_t>(c, tail ? L.tail_first : L.item_first[0]),
-                       at<uint32_t>(c, tail ? L.tail_n : L.n_items[0]), L.NT, L.P,
-                       (uint32_t)slot0);
+                       at<uint32_t>(c, tail ? L.tail_n : L.n_items[0]),
+                       at<uint32_t>(c, tail ? L.tail_used : L.used), L.NT, L.P, (uint32_t)slot0);
     if (n > 0 && lds)
         hipLaunchKernelGGL((k_scatter_lds<NDIM, PS>), dim3(gC), dim3(256), hbytes, s, A, Bo,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n, L.NT, chunk);
@@ -704,29 +731,22 @@ int launch_push(mhdpic_ctx* c, hipStream_t s, bool p) {
     return MHDPIC_OK;
 }
 
-int launch_bin_any(mhdpic_ctx* c, hipStream_t s, int keys) {
+int launch_bin_any(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fields = nullptr) {
     if (c->precision == MHDPIC_FP64) {
-        if (c->ndim == 2) return launch_bin<2, PartF64, double>(c, s, keys);
-        return launch_bin<3, PartF64, double>(c, s, keys);
+        if (c->ndim == 2) return launch_bin<2, PartF64, double>(c, s, keys, fields);
+        return launch_bin<3, PartF64, double>(c, s, keys, fields);
     }
-    if (c->ndim == 2) return launch_bin<2, PartF32, float>(c, s, keys);
-    return launch_bin<3, PartF32, float>(c, s, keys);
+    if (c->ndim == 2) return launch_bin<2, PartF32, float>(c, s, keys, fields);
+    return launch_bin<3, PartF32, float>(c, s, keys, fields);
 }
 
-int launch_fieldprep(mhdpic_ctx* c, const double* B, const double* vg, const double* rho,
-                     hipStream_t s) {
-    const Layout& L = c->L;
-    const int64_t* nJcur = at<int64_t>(c, c->nj == 0 ? L.nJ0 : L.nJ1);
-    int64_t* nJnext = at<int64_t>(c, c->nj == 0 ? L.nJ1 : L.nJ0);
+void launch_fieldprep(mhdpic_ctx* c, hipStream_t s, const StepFields& fields) {
+    const dim3 grid(grid_for(c->L.NC, 256)), block(256);
+    const BoxDev* bd = at<BoxDev>(c, c->L.boxes);
     if (c->precision == MHDPIC_FP64)
-        hipLaunchKernelGGL(k_fieldprep<double>, dim3(grid_for(L.NC, 256)), dim3(256), 0, s,
-                           at<double>(c, L.EB), B, vg, rho, nJcur, nJnext, at<BoxDev>(c, L.boxes),
-                           at<int64_t>(c, L.cell_off), c->nb, L.NC);
+        hipLaunchKernelGGL(k_fieldprep<double>, grid, block, 0, s, field_args<double>(c, fields), bd);
     else
-        hipLaunchKernelGGL(k_fieldprep<float>, dim3(grid_for(L.NC, 256)), dim3(256), 0, s,
-                           at<float>(c, L.EB), B, vg, rho, nJcur, nJnext, at<BoxDev>(c, L.boxes),
-                           at<int64_t>(c, L.cell_off), c->nb, L.NC);
-    return MHDPIC_OK;
+        hipLaunchKernelGGL(k_fieldprep<float>, grid, block, 0, s, field_args<float>(c, fields), bd);
 }
 
 // Event pair around a phase when timing is on.
@@ -846,38 +866,33 @@ int set_dt(mhdpic_ctx* c, const double* dt, int32_t n_sub, hipStream_t s, bool c
     return MHDPIC_OK;
 }
 
-// The kernels of n_steps steps of n_sub particle sub-steps each: re-binning
-// for this call's dt, then per step field preparation and per sub-step the
-// push (n_CR, J_CR at the last sub-step only) and, except after the call's
-// last push, re-binning.
+// The kernels of n_steps steps of n_sub particle sub-steps each: per sub-step
+// the re-binning (the call's first for this call's dt) and the push (n_CR,
+// J_CR at the last sub-step only), and per step the field preparation, in the
+// last launch of its first binning.
 int enqueue_steps(mhdpic_ctx* c, const double* B, const double* vg, const double* rho,
                   int32_t n_steps, int32_t n_sub, hipStream_t s, bool allow_timing,
                   bool codes_valid = false) {
-    if (!rho) rho = B;  // never read without the Hall term
+    const StepFields fields{B, vg, rho ? rho : B};  // (rho: never read without the Hall term)
     const uint32_t saved = c->timing;
     if (!allow_timing) c->timing = 0;
-    int rc;
-    {
-        PhaseTimer t(c, s, 0);
-        rc = launch_bin_any(c, s, codes_valid ? kKeysPushed : kKeysRekey);
-    }
+    const bool apart = (c->timing & 3u) != 0;  // binning and fields timed: launched apart
+    int rc = MHDPIC_OK;
     for (int st = 0; st < n_steps && !rc; ++st) {
-        {
-            PhaseTimer t(c, s, 1);  // also clears the next n_CR, J_CR buffer
-            rc = launch_fieldprep(c, B, vg, rho, s);
-        }
-        if (rc) break;
         for (int sub = 0; sub < n_sub && !rc; ++sub) {
-            const bool last_sub = sub + 1 == n_sub;
             {
-                PhaseTimer t(c, s, 2, true);
-                rc = launch_push(c, s, last_sub);
+                PhaseTimer t(c, s, 0);
+                rc = launch_bin_any(c, s, codes_valid ? kKeysPushed : kKeysRekey,
+                                    sub == 0 && !apart ? &fields : nullptr);
+                codes_valid = true;  // the call's pushes write them
             }
             if (rc) break;
-            if (st + 1 < n_steps || !last_sub) {
-                PhaseTimer t(c, s, 0);
-                rc = launch_bin_any(c, s, kKeysPushed);
+            if (sub == 0 && apart) {
+                PhaseTimer t(c, s, 1);  // also clears the next n_CR, J_CR buffer
+                launch_fieldprep(c, s, fields);
             }
+            PhaseTimer t(c, s, 2, true);
+            rc = launch_push(c, s, sub + 1 == n_sub);
         }
         if (rc) break;
         c->nj = 1 - c->nj;
@@ -1089,7 +1104,7 @@ int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const
     hipLaunchKernelGGL(k_box_tables, dim3(grid_for(nt, 256)), dim3(256), 0, s, bd, nb,
                        at<int64_t>(c, L.part_off), at<int64_t>(c, L.cell_off),
                        at<int32_t>(c, L.tile_box), L.NT);
-    fill_u32(at<uint32_t>(c, L.err), 1, 0u, s);
+    fill_u32(at<uint32_t>(c, L.plan), (L.used + 4 - L.plan) / 4, 0u, s);  // plan, error word, slots
     fill_i64(at<int64_t>(c, L.Dcorr), 4 * L.NC, s);
     fill_i64(at<int64_t>(c, L.nJ0), 4 * L.NC, s);
     c->cur = 0;
@@ -1763,7 +1778,7 @@ int mhdpic_inject(mhdpic_ctx* c, const int64_t* n_new, const double* x, const do
     // removed particles and merges earlier tails
     uint32_t used[2];
     for (int pass = 0;; ++pass) {
-        HIP_TRY(hipMemcpyAsync(&used[0], c->ws + L.start + 4 * (size_t)L.NT, 4, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(&used[0], c->ws + L.used, 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipMemcpyAsync(&used[1], c->ws + L.n_items[c->it], 4, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         const int64_t s0 = (int64_t)used[0] + c->tail;
