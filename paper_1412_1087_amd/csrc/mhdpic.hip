@@ -1156,13 +1156,21 @@ int read_particles(mhdpic_ctx* c, double* x, double* v, hipStream_t s) {
     return MHDPIC_OK;
 }
 
-int read_deposits(mhdpic_ctx* c, int64_t* out, hipStream_t s) {
-    const int64_t NC = c->L.NC;
-    if (NC == 0) return MHDPIC_OK;
-    const int64_t* nJ = at<int64_t>(c, c->nj == 0 ? c->L.nJ0 : c->L.nJ1);
-    HIP_TRY(hipMemcpyAsync(out, nJ, 4 * NC * 8, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipMemcpyAsync(out + 4 * NC, at<int64_t>(c, c->L.Dcorr), 4 * NC * 8,
-                           hipMemcpyDeviceToDevice, s));
+// n_CR, J_CR and the accumulated channels to out; clear: the accumulated ones
+// start again from zero.
+int read_deposits(mhdpic_ctx* c, int64_t* out, bool clear, hipStream_t s) {
+    const int64_t n = 4 * c->L.NC;
+    if (n == 0) return MHDPIC_OK;
+    int64_t* nJ = at<int64_t>(c, c->nj == 0 ? c->L.nJ0 : c->L.nJ1);
+    int64_t* D = at<int64_t>(c, c->L.Dcorr);
+    const auto grid = [](int64_t m) { return dim3((unsigned)std::min<int64_t>(grid_for(m, 256), 8192)); };
+    if ((uintptr_t)out % 16 == 0)  // (n is a multiple of four: so is the second half)
+        hipLaunchKernelGGL(k_deposit_read<longlong2>, grid(n / 2), dim3(256), 0, s, (longlong2*)out,
+                           (const longlong2*)nJ, (longlong2*)D, n / 2, clear);
+    else
+        hipLaunchKernelGGL(k_deposit_read<int64_t>, grid(n), dim3(256), 0, s, out, (const int64_t*)nJ, D, n,
+                           clear);
+    HIP_TRY(hipGetLastError());
     return MHDPIC_OK;
 }
 
@@ -1188,7 +1196,7 @@ int advance_impl(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* np, in
     if (rc) return rc;
     if (n_steps > 0) rc = enqueue_steps(&c, B, vg, rho, n_steps, n_sub, s, false);
     if (!rc) rc = read_particles(&c, x_out, v_out, s);
-    if (!rc) rc = read_deposits(&c, dep_out, s);
+    if (!rc) rc = read_deposits(&c, dep_out, false, s);
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
     return read_error_now(&c, s);
@@ -1660,11 +1668,7 @@ int mhdpic_deposit_read(mhdpic_ctx* c, int64_t* out, int32_t reset_accumulated, 
     if (!c || !out) return fail(MHDPIC_EINVAL, "ctx or out is NULL");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     c->last_stream = s;
-    int rc = read_deposits(c, out, s);
-    if (rc) return rc;
-    if (reset_accumulated) fill_i64(at<int64_t>(c, c->L.Dcorr), 4 * c->L.NC, s);
-    HIP_TRY(hipGetLastError());
-    return MHDPIC_OK;
+    return read_deposits(c, out, reset_accumulated != 0, s);
 }
 
 int mhdpic_feedback(mhdpic_ctx* c, const double* B, const double* vg, const double* rho,
