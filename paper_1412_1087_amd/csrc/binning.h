@@ -365,11 +365,11 @@ constexpr int kMapChunk2D = MHDPIC_MAP_CHUNK_2D;
 // particles are moved one array at a time through LDS (MoveMap, move_step).
 // TAGGED: the context carries particle tags (binary64), moved last; the
 // staging buffer is then 8 bytes per particle in both precisions.
-// MAP: only the ids (and tags) are moved; the kernel writes, for every
-// destination slot, the slot its particle has in A, and the next push reads
-// the particle there and stores it, updated, at the destination (the push
-// reads and writes every particle anyway, so the other arrays need no move
-// of their own).  The push's reads are then gathers, and a level order over
+// MAP: nothing is moved; the kernel writes, for every destination slot, the
+// slot its particle has in A, and the next push reads the particle there and
+// stores it, updated, in the destination's item (the push reads and writes
+// every particle anyway, so the arrays need no move of their own).  The
+// push's reads are then gathers, and a level order over
 // a whole group of isotropic particles, whose residues change at random from
 // step to step, draws the 64 particles of a wave from some 26 lines of
 // 16 slots (a random walk of the residue counts); in 2D the levels therefore
@@ -381,7 +381,8 @@ constexpr int kMapChunk2D = MHDPIC_MAP_CHUNK_2D;
 // nfield blocks of the grid prepare the cell-centred fields of the step that
 // the binning begins (fieldprep_cell), in groups of eight spread evenly over
 // the items' blocks: ranking in LDS and streaming the fields then overlap (a
-// shock box of 8192 x 256 cells: 72 us together, 29 and 57 apart), and a small
+// shock box of 8192 x 256 cells, when the binning also moved ids and tags: 72
+// us together, 29 and 57 apart), and a small
 // step is one launch shorter.  In the plan's launch instead, whose few waves
 // wait on one load after another, the plan took as long as the streaming made
 // its loads wait: 84 us there.
@@ -455,9 +456,7 @@ k_bin_scatter_class(PS A, PS Bo, const uint16_t* __restrict__ code, const uint32
     ItemRegs<BLOCK, uint32_t> rcell;
     ItemRegs<BLOCK, int32_t> rpid;
     ItemRegs<BLOCK, R> rbuf[2];
-    if (MAP) {
-        rpid.load(A.pid, mm);
-    } else {
+    if (!MAP) {
         rcell.load(A.cell, mm);
         rbuf[0].load(rsrc[0], mm);
     }
@@ -546,13 +545,6 @@ k_bin_scatter_class(PS A, PS Bo, const uint16_t* __restrict__ code, const uint32
         for (int u = 0; u < UD; ++u) {
             const int L = threadIdx.x + u * BLOCK;
             if (L < mm.nd) map[mm.goff[mm.grp[L]] + (uint32_t)L] = (uint32_t)mm.begin + mm.from[L];
-        }
-        if (TAGGED) {
-            ItemRegs<BLOCK, double> rtag;
-            move_step<BLOCK>(rpid, Bo.pid, s_stage, rtag, (const double*)A.tag, mm);
-            move_step<BLOCK>(rtag, Bo.tag, s_stage, rcell, (const uint32_t*)nullptr, mm);
-        } else {
-            move_step<BLOCK>(rpid, Bo.pid, s_stage, rcell, (const uint32_t*)nullptr, mm);
         }
         return;
     }

@@ -478,16 +478,15 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fields)
                        PlanShare{at<unsigned long long>(c, L.plan), at<unsigned long long>(c, L.plan + 8)},
                        L.NT, L.P);
     // where the particles move (mhdpic_set_particle_moves): in the push, the
-    // binning moves only the ids (and tags) and leaves the map from new slots
-    // to old ones, through which the push reads the particles and writes them,
-    // updated, to the other buffer; a compaction always moves them itself
+    // binning only leaves a map to their slots, through which the push reads
+    // the particles and writes them, updated, to the other buffer; a compaction
+    // always moves them itself
     const bool map = keys != kKeysStay && c->moves_in_push();
-    // (moving only ids, a block needs few registers: twice the threads per item
+    // (moving nothing, a block needs few registers: twice the threads per item
     // hide more of the ranking's latency)
     constexpr int BM = 512;
-    auto kern = L.tagged ? (map ? k_bin_scatter_class<NDIM, PS, BM, true, true>
-                                : k_bin_scatter_class<NDIM, PS, 256, true, false>)
-                         : (map ? k_bin_scatter_class<NDIM, PS, BM, false, true>
+    auto kern = map ? k_bin_scatter_class<NDIM, PS, BM, false, true>
+                    : (L.tagged ? k_bin_scatter_class<NDIM, PS, 256, true, false>
                                 : k_bin_scatter_class<NDIM, PS, 256, false, false>);
     const int block = map ? BM : 256;
     // (whole groups of eight blocks, so that the items keep their XCDs)

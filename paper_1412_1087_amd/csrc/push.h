@@ -22,11 +22,12 @@ namespace mhdpic {
 
 template <class Pol>
 struct PushArgsT {
-    typename Pol::Part P;        // out: tile-sorted particles (the ids already there)
+    typename Pol::Part P;        // out: tile-sorted particles
     int64_t src_delta;           // bytes from each array of P to the same array of the
                                  // buffer the particles are read from (0: in place)
-    const uint32_t* map;         // slot j of P -> slot of its particle in that buffer;
-                                 // NULL: slot j itself
+    const uint32_t* map;         // the item's j-th particle -> its slot in that buffer (the
+                                 // push then moves it to a slot of the item in P);
+                                 // NULL: slot j itself, updated in place
     uint16_t* code;              // out: code word (pack_code)
     uint32_t* cnt;               // out: [item][code] particle counts
     const typename Pol::R* EB;   // [cells][6] E and B
@@ -208,11 +209,13 @@ __device__ __forceinline__ const T* other_buffer(const T* p, int64_t delta) {
 template <int NDIM, typename R>
 struct PartRec {
     uint32_t cell = 0;
+    int32_t pid = 0;
     R d[3] = {R(0), R(0), R(0)}, v[3] = {R(0), R(0), R(0)};
     R m = R(0), qm = R(0);
     template <typename PS>
     __device__ __forceinline__ void load(const PS& P, int64_t delta, int j) {
         cell = other_buffer(P.cell, delta)[j];
+        pid = other_buffer(P.pid, delta)[j];
         d[0] = other_buffer(P.d[0], delta)[j];
         d[1] = other_buffer(P.d[1], delta)[j];
         d[2] = NDIM == 3 ? other_buffer(P.d[2], delta)[j] : R(0);
@@ -248,10 +251,12 @@ __global__ void __launch_bounds__(BLOCK, (PushShape<Pol, NDIM>::WAVES)) k_push(P
     uint32_t* ncnt = reinterpret_cast<uint32_t*>(F + (size_t)G::NFF * G::FW);  // [NP] centre counts
     constexpr int K = Codes<NDIM>::K;
     __shared__ uint32_t s_cnt[K];
+    __shared__ uint32_t s_fill[2];  // slots taken from the item's front (stayers) and back (movers)
 
     uint32_t item;
     if (!item_of_block(a.n_items, item)) return;
     for (int c = threadIdx.x; c < K; c += BLOCK) s_cnt[c] = 0;
+    if (threadIdx.x < 2) s_fill[threadIdx.x] = 0;
     const WorkItem w = a.items[item];
     const BoxDev bx = a.boxes[w.box];  // a copy: kept in registers across the stores
     if (a.grp >= 0 && bx.grp != a.grp) return;  // a box of another tile shape
@@ -296,8 +301,10 @@ __global__ void __launch_bounds__(BLOCK, (PushShape<Pol, NDIM>::WAVES)) k_push(P
     // have no registers to spare for it
     constexpr bool kPrefetch = PushShape<Pol, NDIM>::PREFETCH;
     PartRec<NDIM, R> nxt;
+    int nsrc = 0;
     if (kPrefetch && j0 < w.end) {
         nxt.load(a.P, a.src_delta, src);
+        nsrc = src;
         if (j0 + BLOCK < w.end) src = src_of(j0 + BLOCK);
     }
     for (int j = j0; j < w.end; j += BLOCK) {
@@ -307,10 +314,13 @@ __global__ void __launch_bounds__(BLOCK, (PushShape<Pol, NDIM>::WAVES)) k_push(P
         int64_t delta = a.src_delta;
         asm volatile("" : "+s"(delta));
         PartRec<NDIM, R> cur;
+        int at = src;  // source slot
         if (kPrefetch) {
             cur = nxt;
+            at = nsrc;
             if (j + BLOCK < w.end) {
                 nxt.load(a.P, delta, src);
+                nsrc = src;
                 if (j + 2 * BLOCK < w.end) src = src_of(j + 2 * BLOCK);
             }
         } else {
@@ -459,30 +469,54 @@ __global__ void __launch_bounds__(BLOCK, (PushShape<Pol, NDIM>::WAVES)) k_push(P
             }
         }
 
-        // store x^(n+1), v^(n+1) and the particle's constants at its slot (a
-        // particle that left keeps only its mark)
-        a.P.cell[j] = gone ? kDeadCell : pack_cell<NDIM>(i[0], i[1], i[2]);
-        a.P.d[0][j] = dl[0];
-        a.P.d[1][j] = dl[1];
-        if (NDIM == 3) a.P.d[2][j] = dl[2];
-        a.P.v[0][j] = vn[0];
-        a.P.v[1][j] = vn[1];
-        a.P.v[2][j] = vn[2];
-        if (a.map) {
-            a.P.m[j] = cur.m;
-            a.P.qm[j] = cur.qm;
-        }
-
         // tile and bank residue of the next half-step cell (the operations of
         // the next step's first drift), or the gone code if that drift takes
         // the particle through an absorbing face
+        uint16_t code;
         const int k = next_code<Pol, NDIM>(bx, T, tx, ty, tz, i, dl, vn, k1.u, hx, hy, hz, gone,
-                                            errbits, a.code[j]);
+                                            errbits, code);
         // most particles stay in the tile: one LDS atomic per wave for them
-        const uint64_t stays = __ballot(k == Codes<NDIM>::STAY);
-        if (k != Codes<NDIM>::STAY && k != Codes<NDIM>::GONE) atomicAdd(&s_cnt[k], 1u);
-        else if (k == Codes<NDIM>::STAY && lane_id() == __ffsll((unsigned long long)stays) - 1)
+        const bool stay = k == Codes<NDIM>::STAY;
+        const uint64_t stays = __ballot(stay);
+        const int lane = lane_id();
+        if (!stay && k != Codes<NDIM>::GONE) atomicAdd(&s_cnt[k], 1u);
+        else if (stay && lane == __ffsll((unsigned long long)stays) - 1)
             atomicAdd(&s_cnt[k], (uint32_t)__popcll(stays));
+
+        // The slot of a moved particle: those that stay in the tile fill the
+        // item from its front, those about to leave it from its back.  The
+        // next push of another tile then reads the leaving ones from
+        // consecutive slots, and this tile's next push the staying ones (left
+        // among the others, each leaving particle costs its reader one
+        // 128-byte line per array: the strip's push read 2040 MB instead of
+        // 1560 and took 757 us instead of 707, the 64^3 beam box's 964 MB
+        // instead of 794).
+        int slot = j;
+        if (a.map) {
+            const uint64_t mine = stay ? stays : __ballot(!stay);
+            const int first = __ffsll((unsigned long long)mine) - 1;
+            uint32_t base = 0;
+            if (lane == first) base = atomicAdd(&s_fill[stay ? 0 : 1], (uint32_t)__popcll(mine));
+            base = (uint32_t)__shfl((int)base, first) + (uint32_t)__popcll(mine & ((1ull << lane) - 1ull));
+            slot = stay ? w.begin + (int)base : w.end - 1 - (int)base;
+        }
+
+        // store x^(n+1), v^(n+1) and the particle's constants at its slot (a
+        // particle that left keeps only its mark)
+        a.code[slot] = code;
+        a.P.cell[slot] = gone ? kDeadCell : pack_cell<NDIM>(i[0], i[1], i[2]);
+        a.P.d[0][slot] = dl[0];
+        a.P.d[1][slot] = dl[1];
+        if (NDIM == 3) a.P.d[2][slot] = dl[2];
+        a.P.v[0][slot] = vn[0];
+        a.P.v[1][slot] = vn[1];
+        a.P.v[2][slot] = vn[2];
+        if (a.map) {
+            a.P.m[slot] = cur.m;
+            a.P.qm[slot] = cur.qm;
+            a.P.pid[slot] = cur.pid;
+            if (a.P.tag) a.P.tag[slot] = other_buffer(a.P.tag, delta)[at];
+        }
     }
     if (errbits) latch(a.err, errbits);
     __syncthreads();
