@@ -216,6 +216,13 @@ struct mhdpic_ctx {
     std::vector<double> codes_dt;
     int32_t codes_nsub = 0;
     int32_t next_id = 0;  // id of the next added particle
+    bool absorbs = false; // a box has an absorbing face
+    // a read-out that uses the other particle buffer: work enqueued on another
+    // stream that also does waits for read_event first (wait_for_read)
+    std::mutex read_mu;
+    hipEvent_t read_event = nullptr;
+    hipStream_t read_stream = nullptr;
+    bool read_pending = false;
     // cached graph of mhdpic_step_graph
     hipGraphExec_t graph_exec = nullptr;
     GraphKey graph_key;
@@ -811,6 +818,20 @@ int post_error_copy(mhdpic_ctx* c, hipStream_t s) {
     return MHDPIC_OK;
 }
 
+// Orders the work that a call is about to enqueue on s after a read-out that
+// was enqueued on another stream and uses the other particle buffer.  The
+// caller holds read_mu.
+int wait_for_read(mhdpic_ctx* c, hipStream_t s) {
+    if (c->read_pending && s != c->read_stream) HIP_TRY(hipStreamWaitEvent(s, c->read_event, 0));
+    c->read_pending = false;
+    return MHDPIC_OK;
+}
+
+int lock_and_wait_for_read(mhdpic_ctx* c, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(c->read_mu);
+    return wait_for_read(c, s);
+}
+
 // Checks the arguments of a step call against the boxes (move limit per box).
 int check_step_boxes(const mhdpic_box* boxes, int32_t nb, int ndim, int64_t NC, const double* B,
                      const double* vg, const double* rho, const double* dt, int32_t n_steps,
@@ -1014,6 +1035,10 @@ int open_context(mhdpic_ctx* c, const mhdpic_box* boxes, int32_t n_boxes, const 
         }
         c->box_grp[b] = g;
     }
+    c->absorbs = false;
+    for (int b = 0; b < n_boxes; ++b)
+        for (int d = 0; d < ndim; ++d)
+            c->absorbs |= boxes[b].boundary[d][0] == MHDPIC_ABSORB || boxes[b].boundary[d][1] == MHDPIC_ABSORB;
     c->L = L;
     c->ws = static_cast<unsigned char*>(workspace);
     return MHDPIC_OK;
@@ -1121,35 +1146,49 @@ int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const
     return read_error_now(c, s);
 }
 
-// Particles in the order of their initial ids into [3][N0] arrays; columns
-// of particles that have left their box read NaN.  Not defined once particles
-// were added (their ids lie beyond N0).
-int read_particles(mhdpic_ctx* c, double* x, double* v, hipStream_t s) {
+// Whether a particle can leave its box (and its columns then read NaN):
+// through an absorbing face or by its tag.
+bool may_leave(const mhdpic_ctx* c) { return c->L.tagged || c->absorbs; }
+
+template <int NDIM, typename PS, typename T>
+void launch_read(mhdpic_ctx* c, double* x, double* v, bool records, hipStream_t s) {
     const Layout& L = c->L;
-    if (c->next_id != c->n_init)
-        return fail(MHDPIC_ESTATE, "particles were added: read them with mhdpic_particles_read_ids");
-    if (c->n_init == 0) return MHDPIC_OK;
     const BoxDev* bd = at<BoxDev>(c, L.boxes);
     const WorkItem* items = at<WorkItem>(c, L.items[c->it]);
     const uint32_t* ni = at<uint32_t>(c, L.n_items[c->it]);
-    const unsigned g = item_grid(L);
-    const double nan = std::nan("");
-    const unsigned gf = (unsigned)std::min<int64_t>(grid_for(3 * c->n_init, 256), 8192);
-    hipLaunchKernelGGL(k_fill_f64, dim3(gf), dim3(256), 0, s, x, 3 * c->n_init, nan);
-    hipLaunchKernelGGL(k_fill_f64, dim3(gf), dim3(256), 0, s, v, 3 * c->n_init, nan);
     const int64_t N = c->n_init;
+    const double nan = std::nan("");
+    const PS P = part<PS, T>(c, c->cur);
+    if (records) {
+        static_assert(sizeof(ReadRec<T>) <= sizeof(T) * (NDIM + 5) + 8, "a slot's arrays hold a record");
+        ReadRec<T>* rec = at<ReadRec<T>>(c, c->cur == 0 ? L.partB : L.partA);
+        if (may_leave(c)) fill_u32(reinterpret_cast<uint32_t*>(rec), N * (int64_t)(sizeof(*rec) / 4), kDeadCell, s);
+        hipLaunchKernelGGL((k_read_records<NDIM, PS>), dim3(item_grid(L)), dim3(256), 0, s, P, rec, items, ni);
+        hipLaunchKernelGGL((k_read_columns<NDIM, T>), dim3(grid_for(N, 256)), dim3(256), 0, s, rec, x, v, bd,
+                           N, nan);
+        return;
+    }
+    const unsigned gf = (unsigned)std::min<int64_t>(grid_for(3 * N, 256), 8192);
+    hipLaunchKernelGGL(k_fill_f64, dim3(gf), dim3(256), 0, s, x, 3 * N, nan);
+    hipLaunchKernelGGL(k_fill_f64, dim3(gf), dim3(256), 0, s, v, 3 * N, nan);
+    hipLaunchKernelGGL((k_read_particles<NDIM, PS>), dim3(item_grid(L)), dim3(256), 0, s, P, x, v, bd, items,
+                       ni, N);
+}
+
+// Particles in the order of their initial ids into [3][N0] arrays; columns
+// of particles that have left their box read NaN.  Not defined once particles
+// were added (their ids lie beyond N0).  records: through the other particle
+// buffer, which no other work may then use before this call's has passed.
+int read_particles(mhdpic_ctx* c, double* x, double* v, bool records, hipStream_t s) {
+    if (c->next_id != c->n_init)
+        return fail(MHDPIC_ESTATE, "particles were added: read them with mhdpic_particles_read_ids");
+    if (c->n_init == 0) return MHDPIC_OK;
     if (c->precision == MHDPIC_FP64) {
-        PartF64 P = part<PartF64, double>(c, c->cur);
-        if (c->ndim == 2)
-            hipLaunchKernelGGL((k_read_particles<2, PartF64>), dim3(g), dim3(256), 0, s, P, x, v, bd, items, ni, N);
-        else
-            hipLaunchKernelGGL((k_read_particles<3, PartF64>), dim3(g), dim3(256), 0, s, P, x, v, bd, items, ni, N);
+        if (c->ndim == 2) launch_read<2, PartF64, double>(c, x, v, records, s);
+        else launch_read<3, PartF64, double>(c, x, v, records, s);
     } else {
-        PartF32 P = part<PartF32, float>(c, c->cur);
-        if (c->ndim == 2)
-            hipLaunchKernelGGL((k_read_particles<2, PartF32>), dim3(g), dim3(256), 0, s, P, x, v, bd, items, ni, N);
-        else
-            hipLaunchKernelGGL((k_read_particles<3, PartF32>), dim3(g), dim3(256), 0, s, P, x, v, bd, items, ni, N);
+        if (c->ndim == 2) launch_read<2, PartF32, float>(c, x, v, records, s);
+        else launch_read<3, PartF32, float>(c, x, v, records, s);
     }
     HIP_TRY(hipGetLastError());
     return MHDPIC_OK;
@@ -1194,7 +1233,7 @@ int advance_impl(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* np, in
     rc = init_device(&c, boxes, np, dt, n_sub, x, v, m, qm, nullptr, s, nullptr);
     if (rc) return rc;
     if (n_steps > 0) rc = enqueue_steps(&c, B, vg, rho, n_steps, n_sub, s, false);
-    if (!rc) rc = read_particles(&c, x_out, v_out, s);
+    if (!rc) rc = read_particles(&c, x_out, v_out, true, s);
     if (!rc) rc = read_deposits(&c, dep_out, false, s);
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
@@ -1375,6 +1414,8 @@ int mhdpic_step_sub(mhdpic_ctx* c, const double* B, const double* vg, const doub
     if (capturing && n_steps % 2)
         return fail(MHDPIC_EINVAL, "a captured call needs an even n_steps");
     c->last_stream = s;
+    if (!capturing) rc = lock_and_wait_for_read(c, s);
+    if (rc) return rc;
     rc = set_dt(c, dt, n_sub, s, capturing);
     if (rc) return rc;
     // an eager call after a push with the same dt and n_sub bins with the
@@ -1408,6 +1449,8 @@ int mhdpic_step_graph_sub(mhdpic_ctx* c, const double* B, const double* vg, cons
     rc = poll_error(c);
     if (rc) return rc;
     c->last_stream = s;
+    rc = lock_and_wait_for_read(c, s);
+    if (rc) return rc;
     // the step constants live in device memory that the graph reads: bring
     // them to this dt first (a no-op when they are current)
     rc = set_dt(c, dt, n_sub, s, false);
@@ -1689,7 +1732,21 @@ int mhdpic_particles_read(mhdpic_ctx* c, double* x, double* v, void* hip_stream)
     if (!c || !x || !v) return fail(MHDPIC_EINVAL, "ctx, x or v is NULL");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     c->last_stream = s;
-    return read_particles(c, x, v, s);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &cap));
+    // (a captured read-out is replayed where no wait orders it against other
+    // streams' calls: it writes to its outputs only)
+    if (cap != hipStreamCaptureStatusNone) return read_particles(c, x, v, false, s);
+    std::lock_guard<std::mutex> lock(c->read_mu);
+    int rc = wait_for_read(c, s);
+    if (rc) return rc;
+    if (!c->read_event) HIP_TRY(hipEventCreateWithFlags(&c->read_event, hipEventDisableTiming));
+    rc = read_particles(c, x, v, true, s);
+    if (rc) return rc;
+    HIP_TRY(hipEventRecord(c->read_event, s));
+    c->read_stream = s;
+    c->read_pending = true;
+    return MHDPIC_OK;
 }
 
 int mhdpic_counts(mhdpic_ctx* c, int64_t* counts, void* hip_stream) {
@@ -1755,6 +1812,8 @@ int mhdpic_inject(mhdpic_ctx* c, const int64_t* n_new, const double* x, const do
     int rc = poll_error(c);
     if (rc) return rc;
     c->last_stream = s;
+    rc = lock_and_wait_for_read(c, s);
+    if (rc) return rc;
     const Layout& L = c->L;
     // offsets of the new particles per box, through a small host buffer
     constexpr int kChunk = 64;
@@ -1903,6 +1962,7 @@ int mhdpic_destroy(mhdpic_ctx* c) {
         (void)hipEventSynchronize(c->err_event);
         (void)hipEventDestroy(c->err_event);
     }
+    if (c->read_event) (void)hipEventDestroy(c->read_event);
     if (c->err_host) (void)hipHostFree(c->err_host);
     delete c;
     return MHDPIC_OK;
