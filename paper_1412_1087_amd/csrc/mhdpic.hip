@@ -541,7 +541,7 @@ int launch_sort(mhdpic_ctx* c, hipStream_t s, int64_t n, int64_t slot0, bool tai
     PS A = shifted(part<PS, T>(c, src), slot0);
     PS Bo = shifted(part<PS, T>(c, dst), slot0);
     const SlotBoxes sb{at<int64_t>(c, L.part_off), c->nb};
-    fill_u32(at<uint32_t>(c, L.count), L.NT, 0u, s);
+    if (tail) fill_u32(at<uint32_t>(c, L.count), L.NT, 0u, s);  // (set-up has cleared them for its sort)
     // per-block LDS histograms when the tiles fit (up to 128 KB of LDS), else
     // one atomic per distinct tile in each wave
     const bool lds = L.NT <= kSortLdsTiles;
@@ -1093,20 +1093,20 @@ void launch_convert(mhdpic_ctx* c, hipStream_t s, const double* x, const double*
 // box records (with the step constants of dt/n_sub when dt is given), the
 // per-box and per-tile tables, conversion of the global positions to (cell,
 // offset) form, the first sort and the n_CR, J_CR deposit at the initial
-// positions (App. A.3 predictor).  The box records pass through a small host
-// buffer in chunks; keep, if given, receives all of them.  Returns the error
-// latched by the kernels.
+// positions (App. A.3 predictor).  The box records travel as kernel arguments;
+// keep, if given, receives all of them.  Returns the error latched by the
+// kernels.
 int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const double* dt,
                 int32_t n_sub, const double* x, const double* v, const double* m,
                 const double* qm, const double* tag, hipStream_t s, BoxDev* keep) {
     const Layout& L = c->L;
     const int nb = c->nb;
-    constexpr int kChunk = 16;
-    BoxDev chunk[kChunk];
+    BoxArgs chunk{};
     int64_t cell_off = 0, part_off = 0;
     int32_t tile_off = 0;
-    for (int b0 = 0; b0 < nb; b0 += kChunk) {
-        const int nc = std::min(kChunk, nb - b0);
+    BoxDev* bd = at<BoxDev>(c, L.boxes);
+    for (int b0 = 0; b0 < nb; b0 += kBoxArgs) {
+        const int nc = std::min(kBoxArgs, nb - b0);
         for (int k = 0; k < nc; ++k) {
             const mhdpic_box& B = boxes[b0 + k];
             BoxDev d = make_boxdev(B, c->ndim, c->box_tile[b0 + k], c->box_grp[b0 + k], cell_off,
@@ -1115,22 +1115,21 @@ int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const
             cell_off += (int64_t)d.n[0] * d.n[1] * d.n[2];
             part_off += np[b0 + k];
             tile_off += d.nt[0] * d.nt[1] * d.nt[2];
-            chunk[k] = d;
+            chunk.box[k] = d;
             if (keep) keep[b0 + k] = d;
         }
-        HIP_TRY(hipMemcpyAsync(c->ws + L.boxes + sizeof(BoxDev) * b0, chunk, sizeof(BoxDev) * nc,
-                               hipMemcpyHostToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));  // the chunk buffer is reused
+        if (nb > kBoxArgs) hipLaunchKernelGGL(k_put_boxes, dim3(1), dim3(256), 0, s, bd, chunk, b0, nc);
     }
     c->dt_uploaded = dt != nullptr;
-    const BoxDev* bd = at<BoxDev>(c, L.boxes);
-    const int64_t nt = std::max<int64_t>(L.NT, nb + 1);
-    hipLaunchKernelGGL(k_box_tables, dim3(grid_for(nt, 256)), dim3(256), 0, s, bd, nb,
-                       at<int64_t>(c, L.part_off), at<int64_t>(c, L.cell_off),
-                       at<int32_t>(c, L.tile_box), L.NT);
-    fill_u32(at<uint32_t>(c, L.plan), (L.used + 4 - L.plan) / 4, 0u, s);  // plan, error word, slots
-    fill_i64(at<int64_t>(c, L.Dcorr), 4 * L.NC, s);
-    fill_i64(at<int64_t>(c, L.nJ0), 4 * L.NC, s);
+    // cleared: the accumulated deposits and n_CR, J_CR (neighbours in the
+    // workspace), the tile counts, and plan, error word and slots
+    const auto words = [](size_t bytes) { return (int64_t)(bytes / 8); };
+    const ClearArgs ca{{at<uint64_t>(c, L.Dcorr), at<uint64_t>(c, L.count), at<uint64_t>(c, L.plan)},
+                       {words(L.nJ1 - L.Dcorr), words(L.cursor - L.count), words(L.boxes - L.plan)}};
+    const int64_t most = std::max<int64_t>({L.NT, nb + 1, ca.n[0]});
+    hipLaunchKernelGGL(k_setup, dim3((unsigned)std::min<int64_t>(grid_for(most, 256), 4096)), dim3(256), 0, s,
+                       bd, chunk, nb <= kBoxArgs, nb, at<int64_t>(c, L.part_off), at<int64_t>(c, L.cell_off),
+                       at<int32_t>(c, L.tile_box), L.NT, ca);
     c->cur = 0;
     c->nj = 0;
     launch_convert(c, s, x, v, m, qm, tag, L.N0, 0, 0, c->cur);
@@ -1216,7 +1215,7 @@ int read_deposits(mhdpic_ctx* c, int64_t* out, bool clear, hipStream_t s) {
 // a context that lives on this function's stack and in `ws` (nothing of it is
 // kept): open, set up with the step constants, n_steps steps, read back.
 // Waits for the stream.  Host memory: the context's fixed fields and a
-// 16-record staging buffer, both on the stack.
+// few box records, both on the stack.
 int advance_impl(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* np, int32_t precision,
                  const double* x, const double* v, const double* m, const double* qm,
                  const double* B, const double* vg, const double* rho, const double* dt,
