@@ -80,13 +80,15 @@ __global__ void k_fill_i64(int64_t* p, int64_t n) {
 }
 
 // The deposits read out: n elements of nJ to out, and as many of D after them,
-// with D cleared if `clear`.  V: the widest access out is aligned to (a pair
+// with D cleared if `clear`; nothing if skip is given and *skip set.  V: the widest access out is aligned to (a pair
 // at a time, or its two halves).  One launch, bound by memory, in place of two
 // copies and a fill: 2.1 M cells (8192 x 256) took 72 us and take 53,
 // and a step of a 32^2 box with its read-out went from 39.5 to 35.5 us.
 template <typename V>
 __global__ void __launch_bounds__(256)
-k_deposit_read(V* __restrict__ out, const V* __restrict__ nJ, V* __restrict__ D, int64_t n, bool clear) {
+k_deposit_read(V* __restrict__ out, const V* __restrict__ nJ, V* __restrict__ D, int64_t n, bool clear,
+               const uint32_t* skip) {
+    if (skip && *skip) return;
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
         const V a = nJ[i], b = D[i];
@@ -716,7 +718,7 @@ __global__ void k_read_particles(PS P, double* __restrict__ x, double* __restric
 
 // The same read-out through records: k_read_records writes each particle's
 // state to the record of its id, and k_read_columns turns the records into the
-// columns.  Ids lie at random against slots, and a store of 8 bytes then costs
+// columns (or does nothing if skip is given and *skip set).  Ids lie at random against slots, and a store of 8 bytes then costs
 // as much as one of a half or whole 64-byte line; k_read_particles has six of
 // them per particle, and its outputs a fill before.  A record is half a line
 // (binary32) or one (binary64), written by one lane, in the other particle
@@ -755,7 +757,8 @@ k_read_records(PS P, ReadRec<typename PS::R>* __restrict__ rec, const WorkItem* 
 template <int NDIM, typename R>
 __global__ void __launch_bounds__(256)
 k_read_columns(const ReadRec<R>* __restrict__ rec, double* __restrict__ x, double* __restrict__ v,
-               const BoxDev* __restrict__ boxes, int64_t N, double nan) {
+               const BoxDev* __restrict__ boxes, int64_t N, double nan, const uint32_t* skip) {
+    if (skip && *skip) return;
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= N) return;
     const ReadRec<R> r = rec[p];
