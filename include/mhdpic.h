@@ -98,7 +98,9 @@ typedef struct {
                                (the boxes of one context may differ);
                                0 = library default (2D: 32x16; 3D: 8x4x4, or
                                4x4x4 for a box given 24 or more particles per
-                               cell).  tile[2] is ignored in 2D */
+                               cell; contexts of few tiles get the smallest of
+                               8x8, 16x16 or 4x4x4 that still makes few).
+                               tile[2] is ignored in 2D */
     int32_t boundary[3][2]; /* per axis, low and high face: MHDPIC_PERIODIC (both faces or
                                neither), MHDPIC_REFLECT or MHDPIC_ABSORB; all zero =
                                periodic.  A non-periodic axis needs at least 2 cells */

@@ -92,14 +92,44 @@ bool tile_supported(int ndim, int prec, const TileShape& t) {
 // around every timed launch).
 constexpr unsigned kTimingEventFlags = hipEventDisableSystemFence;
 
-// The library's tile for a box of `cells` cells and np particles: in 3D the
-// shape that holds about 2048 particles (measured on the beam boxes: 8x4x4
-// at 16 per cell, 4x4x4 at 32, in both precisions).
-TileShape default_tile(int ndim, int64_t cells, int64_t np) {
-    if (ndim == 2) return {32, 16, 1};
-    if (cells > 0 && np >= 24 * cells) return {4, 4, 4};
-    return {8, 4, 4};
+int64_t tile_count(const mhdpic_box& B, const TileShape& t) {
+    int64_t n = 1;
+    const int32_t T[3] = {t.x, t.y, t.z};
+    for (int d = 0; d < B.ndim && d < 3; ++d) n *= ((int64_t)std::clamp(B.n[d], 1, 65536) + T[d] - 1) / T[d];
+    return n;
 }
+
+// The library's tile for boxes that give none.  Large contexts: 32x16, in 3D
+// the shape that holds about 2048 particles (measured on the beam boxes: 8x4x4
+// at 16 per cell, 4x4x4 at 32, in both precisions).  Small contexts: the
+// smallest shape whose tiles, over all boxes, stay within one per CU (256), in
+// 3D, where a tile's ghost cells outnumber its own, half of that: each tile is
+// at least one block of the push, a block takes long however few there are,
+// and more of them than CUs only add ghost cells.  A step, 2D with 16 per cell,
+// by 32x16, 16x16 and 8x8: 32^2 26, 24 and 24 us; 128^2 (32, 64 and 256 tiles)
+// 53, 45 and 38; 256^2 with 2 per cell (128, 256 and 1024) 41, 34 and 44; 512^2
+// (512, 1024) 65 and 70.  3D, 2 per cell, by 8x4x4 and 4x4x4: 16^3 (64 tiles of
+// 4x4x4) 35 and 29, 32^3 (512) 42 and 48; with 16 per cell 24^3 (216) 64 and 70.
+struct DefaultTiles {
+    bool t8 = true, t16 = true, t4 = true;  // within their limits
+    // plain: the large contexts' shapes, whatever the size
+    DefaultTiles(const mhdpic_box* boxes, int32_t nb, bool plain) {
+        int64_t n8 = 0, n16 = 0, n4 = 0;
+        for (int b = 0; b < nb; ++b) {
+            n8 += tile_count(boxes[b], {8, 8, 1});
+            n16 += tile_count(boxes[b], {16, 16, 1});
+            n4 += tile_count(boxes[b], {4, 4, 4});
+        }
+        t8 = !plain && n8 <= 256;
+        t16 = !plain && n16 <= 256;
+        t4 = !plain && n4 <= 128;
+    }
+    TileShape shape(int ndim, int64_t cells, int64_t np) const {
+        if (ndim == 2) return t8 ? TileShape{8, 8, 1} : (t16 ? TileShape{16, 16, 1} : TileShape{32, 16, 1});
+        if (t4 || (cells > 0 && np >= 24 * cells)) return {4, 4, 4};
+        return {8, 4, 4};
+    }
+};
 
 // Particles per work item, at most: the largest power of two up to 4096 that
 // gives an item for each of the 256 CUs, else 512, one pass of the push's
@@ -234,13 +264,14 @@ struct mhdpic_ctx {
 namespace {
 
 int validate_boxes(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32_t precision,
-                   int& ndim, std::vector<TileShape>& tiles) {
+                   int& ndim, std::vector<TileShape>& tiles, bool plain = false) {
     if (!boxes || nb < 1 || !np) return fail(MHDPIC_EINVAL, "boxes, n_boxes or n_particles invalid");
     if (precision != MHDPIC_FP64 && precision != MHDPIC_FP32_MIXED)
         return fail(MHDPIC_EINVAL, "precision must be MHDPIC_FP64 or MHDPIC_FP32_MIXED");
     ndim = boxes[0].ndim;
     if (ndim != 2 && ndim != 3) return fail(MHDPIC_EINVAL, "ndim must be 2 or 3");
     tiles.assign(nb, TileShape{});
+    const DefaultTiles defaults(boxes, nb, plain);
     int64_t N = 0, NC = 0;
     for (int b = 0; b < nb; ++b) {
         const mhdpic_box& B = boxes[b];
@@ -249,7 +280,7 @@ int validate_boxes(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
         if (t.x == 0 && t.y == 0) {
             int64_t cells = 1;
             for (int d = 0; d < ndim; ++d) cells *= std::max<int64_t>(B.n[d], 0);
-            t = default_tile(ndim, cells, np[b]);
+            t = defaults.shape(ndim, cells, np[b]);
         }
         if (!tile_supported(ndim, precision, t))
             return fail(MHDPIC_ENOTSUP, "tile shape has no compiled kernel or exceeds the LDS");
@@ -1015,9 +1046,13 @@ int open_context(mhdpic_ctx* c, const mhdpic_box* boxes, int32_t n_boxes, const 
     Layout L = make_layout(boxes, n_boxes, np, precision, ndim, tiles);
     if (!workspace) return fail(MHDPIC_EINVAL, "workspace is NULL");
     if (((uintptr_t)workspace) % kAlign) return fail(MHDPIC_EINVAL, "workspace must be 256-byte aligned");
-    // (smaller items take some more workspace: a workspace that only holds the
-    // layout with the largest ones gets that)
-    if (ws_bytes < L.total) L = make_layout(boxes, n_boxes, np, precision, ndim, tiles, true);
+    // (smaller tiles and items take some more workspace: one that only holds
+    // the layout with the largest ones gets that)
+    if (ws_bytes < L.total) {
+        rc = validate_boxes(boxes, n_boxes, np, precision, ndim, tiles, true);
+        if (rc) return rc;
+        L = make_layout(boxes, n_boxes, np, precision, ndim, tiles, true);
+    }
     if (ws_bytes < L.total) return fail(MHDPIC_ENOMEM, "workspace too small");
     if (L.N0 > 0 && (!x || !v || !m || !qm)) return fail(MHDPIC_EINVAL, "particle arrays are NULL");
     c->ndim = ndim;
@@ -1381,7 +1416,7 @@ int mhdpic_advance_noalloc(const mhdpic_box* boxes, int32_t n_boxes, const int64
                            double* v_out, int64_t* deposits_out, void* hip_stream) {
     int ndim;
     std::vector<TileShape> tiles;
-    int rc = validate_boxes(boxes, n_boxes, n_particles, precision, ndim, tiles);
+    int rc = validate_boxes(boxes, n_boxes, n_particles, precision, ndim, tiles, true);
     if (rc) return rc;
     const size_t need = make_layout(boxes, n_boxes, n_particles, precision, ndim, tiles, true).total;
     if (need > kScratchBytes) {
