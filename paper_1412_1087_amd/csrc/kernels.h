@@ -168,22 +168,22 @@ k_setup(BoxDev* __restrict__ boxes, BoxArgs a, bool put, int nb, int64_t* __rest
         for (int64_t i = i0; i < ca.n[r]; i += stride) ca.p[r][i] = 0;
 }
 
-// Converts new particles j = 0 .. N-1 (global positions x, four-velocities
-// v, [3][N]; m, qm, optional tags, [N]) of the boxes new_off[] describes
-// into slots slot0 + j of P, with ids pid0 + j.  Without tags a particle's
-// tag is +infinity (no removal by tag ever takes it).
-template <int NDIM, typename PS, typename T>
-__global__ void k_init_convert(PS P, const double* __restrict__ x, const double* __restrict__ v,
-                               const double* __restrict__ m, const double* __restrict__ qm,
-                               const double* __restrict__ tag, const BoxDev* __restrict__ boxes,
-                               const int64_t* __restrict__ new_off, int nb, int64_t N,
-                               int64_t slot0, int32_t pid0, uint32_t* err) {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    int b = find_box(new_off, nb, j);
-    const BoxDev& bx = boxes[b];
-    const int64_t sl = slot0 + j;
-    int ic[3] = {0, 0, 0};
+// A new particle: packed cell, offset in it, four-velocity, m and q/m.
+template <int NDIM, typename T>
+struct NewParticle {
+    T d[NDIM], v[3], m, qm;
+    uint32_t cell;
+};
+
+// New particle j of N (global positions x, four-velocities v, [3][N]; m, qm,
+// [N]) of box bx; ic receives its cell.
+template <int NDIM, typename T>
+__device__ __forceinline__ NewParticle<NDIM, T>
+new_particle(const double* __restrict__ x, const double* __restrict__ v, const double* __restrict__ m,
+             const double* __restrict__ qm, const BoxDev& bx, int64_t N, int64_t j, int ic[3],
+             uint32_t* err) {
+    NewParticle<NDIM, T> r;
+    ic[0] = ic[1] = ic[2] = 0;
     bool bad = false, far = false;
     for (int d = 0; d < NDIM; ++d) {
         double s = (x[d * N + j] - bx.x0[d]) / bx.dx[d];
@@ -204,19 +204,47 @@ __global__ void k_init_convert(PS P, const double* __restrict__ x, const double*
                 ic[d] = wrap_shift(ic[d], 1, bx.n[d]);
             }
         }
-        P.d[d][sl] = o;
+        r.d[d] = o;
     }
     for (int d = 0; d < 3; ++d) {
         double vd = v[d * N + j];
         if (!isfinite(vd)) bad = true;
-        P.v[d][sl] = (T)vd;
+        r.v[d] = (T)vd;
     }
     if (!isfinite(m[j]) || !isfinite(qm[j])) bad = true;
     if (bad) latch(err, ERRBIT_NONFINITE);
     if (far) latch(err, ERRBIT_RANGE);
-    P.cell[sl] = pack_cell<NDIM>(ic[0], ic[1], ic[2]);
-    P.m[sl] = m[j];
-    P.qm[sl] = qm[j];
+    r.cell = pack_cell<NDIM>(ic[0], ic[1], ic[2]);
+    r.m = m[j];
+    r.qm = qm[j];
+    return r;
+}
+
+// Stores r at slot sl of P.
+template <int NDIM, typename PS, typename T>
+__device__ __forceinline__ void store_new(const PS& P, int64_t sl, const NewParticle<NDIM, T>& r) {
+    for (int d = 0; d < NDIM; ++d) P.d[d][sl] = r.d[d];
+    for (int d = 0; d < 3; ++d) P.v[d][sl] = r.v[d];
+    P.cell[sl] = r.cell;
+    P.m[sl] = r.m;
+    P.qm[sl] = r.qm;
+}
+
+// Converts new particles j = 0 .. N-1 (global positions x, four-velocities
+// v, [3][N]; m, qm, optional tags, [N]) of the boxes new_off[] describes
+// into slots slot0 + j of P, with ids pid0 + j.  Without tags a particle's
+// tag is +infinity (no removal by tag ever takes it).
+template <int NDIM, typename PS, typename T>
+__global__ void k_init_convert(PS P, const double* __restrict__ x, const double* __restrict__ v,
+                               const double* __restrict__ m, const double* __restrict__ qm,
+                               const double* __restrict__ tag, const BoxDev* __restrict__ boxes,
+                               const int64_t* __restrict__ new_off, int nb, int64_t N,
+                               int64_t slot0, int32_t pid0, uint32_t* err) {
+    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= N) return;
+    int ic[3];
+    const int64_t sl = slot0 + j;
+    store_new<NDIM>(P, sl, new_particle<NDIM, T>(x, v, m, qm, boxes[find_box(new_off, nb, j)], N, j, ic, err));
     P.pid[sl] = pid0 + (int32_t)j;
     if (P.tag) P.tag[sl] = tag ? tag[j] : (double)INFINITY;
 }

@@ -563,9 +563,75 @@ PS shifted(PS P, int64_t off) {
     return P;
 }
 
+// Input arrays of new particles.
+struct NewArrays {
+    const double *x, *v, *m, *qm;
+};
+
+// Launch shape of the sorts with per-block LDS histograms: each block takes
+// `chunk` consecutive particles.  (Few particles: smaller chunks, so that they
+// fill the chip; each block also goes over all the tiles.)
+struct SortShape {
+    int chunk = 256;
+    unsigned grid;
+    size_t hbytes;
+    SortShape(int64_t n, int32_t NT) {
+        while (chunk < kSortChunk && (n > (int64_t)chunk * 1024 || chunk < NT)) chunk *= 2;
+        grid = (unsigned)((n + chunk - 1) / chunk);
+        hbytes = (size_t)NT * sizeof(uint32_t);
+    }
+};
+
+int allow_lds(const void* kern, size_t bytes) {
+    if (bytes > 65536) HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    return MHDPIC_OK;
+}
+
+void launch_scan(mhdpic_ctx* c, hipStream_t s, int64_t slot0, bool tail) {
+    const Layout& L = c->L;
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, at<uint32_t>(c, L.count),
+                       at<uint32_t>(c, L.cursor), at<int32_t>(c, L.tile_box),
+                       at<WorkItem>(c, tail ? L.tail_items : L.items[0]),
+                       at<uint32_t>(c, tail ? L.tail_first : L.item_first[0]),
+                       at<uint32_t>(c, tail ? L.tail_n : L.n_items[0]),
+                       at<uint32_t>(c, tail ? L.tail_used : L.used), L.NT, L.P, (uint32_t)slot0);
+}
+
+// The first sort of a context from the input arrays: N0 new particles, keyed
+// and ranked by the tile of their cell, into the buffer that becomes current,
+// with the work list in list 0.  For NT <= kSortLdsTiles.
+template <int NDIM, typename PS, typename T>
+int launch_first_sort(mhdpic_ctx* c, hipStream_t s, const NewArrays& in) {
+    const Layout& L = c->L;
+    using Rec = NewParticle<NDIM, T>;
+    static_assert(sizeof(Rec) <= sizeof(T) * (NDIM + 5) + 8, "a slot's arrays hold a record");
+    Rec* rec = at<Rec>(c, c->cur == 0 ? L.partA : L.partB);
+    const PS P = part<PS, T>(c, 1 - c->cur);
+    const SortShape sh(L.N0, L.NT);
+    int rc = allow_lds((const void*)k_init_records<NDIM, PS>, sh.hbytes);
+    if (!rc) rc = allow_lds((const void*)k_init_rank, sh.hbytes);
+    if (rc) return rc;
+    if (L.N0 > 0)
+        hipLaunchKernelGGL((k_init_records<NDIM, PS>), dim3(sh.grid), dim3(256), sh.hbytes, s, rec, in.x, in.v,
+                           in.m, in.qm, at<uint32_t>(c, L.key), at<uint32_t>(c, L.count),
+                           at<BoxDev>(c, L.boxes), SlotBoxes{at<int64_t>(c, L.part_off), c->nb}, L.N0, L.NT,
+                           sh.chunk, at<uint32_t>(c, L.err));
+    launch_scan(c, s, 0, false);
+    if (L.N0 > 0) {
+        hipLaunchKernelGGL(k_init_rank, dim3(sh.grid), dim3(256), sh.hbytes, s, P.pid, at<uint32_t>(c, L.key),
+                           at<uint32_t>(c, L.cursor), L.N0, L.NT, sh.chunk);
+        hipLaunchKernelGGL((k_init_gather<NDIM, PS>), dim3(grid_for(L.N0, 256)), dim3(256), 0, s, P, rec, L.N0);
+    }
+    c->cur = 1 - c->cur;
+    c->it = 0;
+    c->tail = 0;
+    return MHDPIC_OK;
+}
+
 // Sorts n particles by the tile of their cell (the boxes the part_off table
 // lists, box by box), dropping those that have left their box.
-//   first sort of a context: buffer cur slots [0, n) -> the other buffer,
+//   first sort of a context (that launch_first_sort does not take): buffer cur
+//     slots [0, n) -> the other buffer,
 //     which becomes current, with the work list rebuilt in list 0;
 //   tail (added particles): the other buffer's slots [slot0, slot0 + n) ->
 //     the current buffer's same slots, with the tail's work list in the
@@ -581,35 +647,24 @@ int launch_sort(mhdpic_ctx* c, hipStream_t s, int64_t n, int64_t slot0, bool tai
     // per-block LDS histograms when the tiles fit (up to 128 KB of LDS), else
     // one atomic per distinct tile in each wave
     const bool lds = L.NT <= kSortLdsTiles;
-    // (few particles: smaller chunks, so that they fill the chip; each block
-    // also goes over all the tiles)
-    int chunk = 256;
-    while (chunk < kSortChunk && (n > (int64_t)chunk * 1024 || chunk < L.NT)) chunk *= 2;
-    const unsigned gC = (unsigned)((n + chunk - 1) / chunk);
-    const size_t hbytes = (size_t)L.NT * sizeof(uint32_t);
-    if (lds && hbytes > 65536) {
-        HIP_TRY(hipFuncSetAttribute((const void*)k_key_count_lds<NDIM, PS>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)hbytes));
-        HIP_TRY(hipFuncSetAttribute((const void*)k_scatter_lds<NDIM, PS>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)hbytes));
+    const SortShape sh(n, L.NT);
+    if (lds) {
+        int rc = allow_lds((const void*)k_key_count_lds<NDIM, PS>, sh.hbytes);
+        if (!rc) rc = allow_lds((const void*)k_scatter_lds<NDIM, PS>, sh.hbytes);
+        if (rc) return rc;
     }
     if (n > 0 && lds)
-        hipLaunchKernelGGL((k_key_count_lds<NDIM, PS>), dim3(gC), dim3(256), hbytes, s, A,
+        hipLaunchKernelGGL((k_key_count_lds<NDIM, PS>), dim3(sh.grid), dim3(256), sh.hbytes, s, A,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.count), at<BoxDev>(c, L.boxes),
-                           sb, n, L.NT, chunk);
+                           sb, n, L.NT, sh.chunk);
     else if (n > 0)
         hipLaunchKernelGGL((k_key_cell<NDIM, PS>), dim3(grid_for(n, 256)), dim3(256), 0, s, A,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.count), at<BoxDev>(c, L.boxes),
                            sb, n);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, at<uint32_t>(c, L.count),
-                       at<uint32_t>(c, L.cursor), at<int32_t>(c, L.tile_box),
-                       at<WorkItem>(c, tail ? L.tail_items : L.items[0]),
-                       at<uint32_t>(c, tail ? L.tail_first : L.item_first[0]),
-                       at<uint32_t>(c, tail ? L.tail_n : L.n_items[0]),
-                       at<uint32_t>(c, tail ? L.tail_used : L.used), L.NT, L.P, (uint32_t)slot0);
+    launch_scan(c, s, slot0, tail);
     if (n > 0 && lds)
-        hipLaunchKernelGGL((k_scatter_lds<NDIM, PS>), dim3(gC), dim3(256), hbytes, s, A, Bo,
-                           at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n, L.NT, chunk);
+        hipLaunchKernelGGL((k_scatter_lds<NDIM, PS>), dim3(sh.grid), dim3(256), sh.hbytes, s, A, Bo,
+                           at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n, L.NT, sh.chunk);
     else if (n > 0)
         hipLaunchKernelGGL((k_scatter<NDIM, PS>), dim3(grid_for(n, 256)), dim3(256), 0, s, A, Bo,
                            at<uint32_t>(c, L.key), at<uint32_t>(c, L.cursor), n);
@@ -1139,7 +1194,7 @@ void launch_convert(mhdpic_ctx* c, hipStream_t s, const double* x, const double*
 // kernels.
 int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const double* dt,
                 int32_t n_sub, const double* x, const double* v, const double* m,
-                const double* qm, const double* tag, hipStream_t s, BoxDev* keep, bool wait) {
+                const double* qm, hipStream_t s, BoxDev* keep, bool wait) {
     const Layout& L = c->L;
     const int nb = c->nb;
     BoxArgs chunk{};
@@ -1173,10 +1228,21 @@ int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const
                        at<int32_t>(c, L.tile_box), L.NT, ca);
     c->cur = 0;
     c->nj = 0;
-    launch_convert(c, s, x, v, m, qm, tag, L.N0, 0, 0, c->cur);
     c->n_init = L.N0;
     c->next_id = (int32_t)L.N0;
-    int rc = launch_sort_any(c, s, L.N0, 0, false);
+    int rc;
+    if (L.NT <= kSortLdsTiles) {
+        const NewArrays in{x, v, m, qm};
+        if (c->precision == MHDPIC_FP64)
+            rc = c->ndim == 2 ? launch_first_sort<2, PartF64, double>(c, s, in)
+                              : launch_first_sort<3, PartF64, double>(c, s, in);
+        else
+            rc = c->ndim == 2 ? launch_first_sort<2, PartF32, float>(c, s, in)
+                              : launch_first_sort<3, PartF32, float>(c, s, in);
+    } else {
+        launch_convert(c, s, x, v, m, qm, nullptr, L.N0, 0, 0, c->cur);
+        rc = launch_sort_any(c, s, L.N0, 0, false);
+    }
     if (rc) return rc;
     if (L.N0 > 0) {
         rc = launch_init_deposit(c, s);
@@ -1276,7 +1342,7 @@ int advance_impl(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* np, in
     // move nothing), so what set-up refuses is found at the end; a 64^2 box's
     // advance went from 180 to 157 us
     c.one_call = n_steps > 0;
-    rc = init_device(&c, boxes, np, dt, n_sub, x, v, m, qm, nullptr, s, nullptr, !c.one_call);
+    rc = init_device(&c, boxes, np, dt, n_sub, x, v, m, qm, s, nullptr, !c.one_call);
     if (rc) return rc;
     if (n_steps > 0) rc = enqueue_steps(&c, B, vg, rho, n_steps, n_sub, s, false);
     if (!rc) rc = read_particles(&c, x_out, v_out, true, s);
@@ -1393,7 +1459,7 @@ int init_ctx(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* n_particle
     if (!rc) {
         c->boxes.assign(boxes, boxes + n_boxes);
         c->bdev.resize(n_boxes);
-        rc = init_device(c, boxes, n_particles, nullptr, 1, x, v, m, qm, nullptr, s, c->bdev.data(), true);
+        rc = init_device(c, boxes, n_particles, nullptr, 1, x, v, m, qm, s, c->bdev.data(), true);
     }
     if (rc) {
         if (c->err_host) (void)hipHostFree(c->err_host);
