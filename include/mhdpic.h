@@ -355,9 +355,9 @@ int mhdpic_timing_read(mhdpic_ctx* ctx, double* ms, int64_t* launches);
 
 /* Where the particles of a step move to their new slots.  Before each push
  * the particles are binned by the tile of the cell they have reached.
- *   MHDPIC_MOVES_IN_PUSH: the binning moves only the ids (and tags) and
- *     leaves a map from new slots to old ones; the push reads each particle
- *     through it and writes it, updated, to its new slot.  This saves a pass
+ *   MHDPIC_MOVES_IN_PUSH: the binning moves nothing and leaves a map to the
+ *     particles' slots; the push reads each particle through it and writes
+ *     it, updated, to the other particle buffer.  This saves a pass
  *     over the particle data, but the push's reads become gathers, whose
  *     cost grows the more the particles of a tile change cells in different
  *     ways from one step to the next;

@@ -6,10 +6,11 @@
 // particle's next tile is given by a direction code relative to the tile of
 // the work item that processed it: code = (cz*3 + cy)*3 + cx with c = 0, 1, 2
 // for -1, 0, +1 tiles (2D: cy*3 + cx).  A work item counts its particles per
-// code in LDS and stores the counts; one scan block turns all counts into the
+// code in LDS and stores the counts; the plan turns all counts into the
 // destination offset of every (item, code) group and into the next work list;
-// the scatter then moves each particle to its group's offset plus a rank taken
-// from an LDS counter.  No counter is shared between blocks.
+// the scatter then moves each particle (or maps it: the push moves it) to its
+// group's offset plus a rank taken from an LDS counter.  No counter of
+// particles is shared between blocks.
 #pragma once
 #include "kernels.h"
 #include "push.h"
@@ -420,6 +421,7 @@ k_bin_scatter_class(PS A, PS Bo, const uint16_t* __restrict__ code, const uint32
     __shared__ uint32_t s_off[NG], s_lbase[NG], s_nd;
     __shared__ uint16_t s_src[kItemParticles];
     __shared__ uint8_t s_grp[kItemParticles];
+    static_assert(!(TAGGED && MAP), "a map moves no tags");
     using SR = typename std::conditional<
         TAGGED, double, typename std::conditional<MAP, uint32_t, typename PS::R>::type>::type;
     __shared__ SR s_stage[kItemParticles];

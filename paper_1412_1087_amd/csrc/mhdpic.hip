@@ -1,12 +1,12 @@
 // Host runtime and C ABI of the MHD-PIC cosmic-ray particle library.
 //
 // Per mhdpic_step call (fields fixed, dt per box):
-//   rekey -> scan -> scatter          bin particles by the tile of x^(n+1/2)
+//   rekey                             code words for this dt
 //   per step:
-//     fieldprep                       cell-centred E (Sec. 2.1)
+//     plan -> scatter                 bin particles by the tile of x^(n+1/2);
+//                                     beside it the cell-centred E (Sec. 2.1)
 //     push                            gather + Boris + deposits (App. A.2, A.3);
 //                                     also counts particles per next tile
-//     scan -> scatter (not after the last step)
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
