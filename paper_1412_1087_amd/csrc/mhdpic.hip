@@ -494,6 +494,13 @@ FieldArgs<T> field_args(mhdpic_ctx* c, const StepFields& f) {
     return fa;
 }
 
+// The fields in a launch of their own.
+template <typename T>
+void launch_fields(mhdpic_ctx* c, hipStream_t s, const StepFields& f) {
+    hipLaunchKernelGGL(k_fieldprep<T>, dim3(grid_for(c->L.NC, 256)), dim3(256), 0, s, field_args<T>(c, f),
+                       at<BoxDev>(c, c->L.boxes));
+}
+
 // Re-bins the particles of the current buffer into the other one, and
 // prepares the fields of the step that begins with it, if given.
 template <int NDIM, typename PS, typename T>
@@ -532,12 +539,18 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fields)
                     : (L.tagged ? k_bin_scatter_class<NDIM, PS, 256, true, false>
                                 : k_bin_scatter_class<NDIM, PS, 256, false, false>);
     const int block = map ? BM : 256;
-    // (whole groups of eight blocks, so that the items keep their XCDs)
-    const unsigned nfield = fields ? (grid_for(L.NC, block) + 7) / 8 * 8 : 0;
+    // fields: beside the scatter, in whole groups of eight blocks, so that the
+    // items keep their XCDs; in a launch of their own where the two together
+    // reach the 2^32 threads that a launch has to stay below (8.6 x 10^8 cells in
+    // tiles of 8x4x4)
+    const unsigned ngroups = (grid_for(L.NC, block) + 7) / 8 * 8;
+    const bool beside = fields && ((uint64_t)item_grid(L) + ngroups) * (uint64_t)block < 1ull << 32;
+    const unsigned nfield = beside ? ngroups : 0;
     hipLaunchKernelGGL(kern, dim3(item_grid(L) + nfield), dim3(block), 0, s, A, Bo,
                        at<uint16_t>(c, L.code), at<uint32_t>(c, L.off), at<WorkItem>(c, L.items[it]),
                        at<uint32_t>(c, L.n_items[it]), at<uint32_t>(c, L.key), bd,
-                       fields ? field_args<T>(c, *fields) : FieldArgs<T>{}, nfield);
+                       beside ? field_args<T>(c, *fields) : FieldArgs<T>{}, nfield);
+    if (fields && !beside) launch_fields<T>(c, s, *fields);
     if (map)
         c->map_pending = true;
     else
@@ -838,12 +851,10 @@ int launch_bin_any(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fie
 }
 
 void launch_fieldprep(mhdpic_ctx* c, hipStream_t s, const StepFields& fields) {
-    const dim3 grid(grid_for(c->L.NC, 256)), block(256);
-    const BoxDev* bd = at<BoxDev>(c, c->L.boxes);
     if (c->precision == MHDPIC_FP64)
-        hipLaunchKernelGGL(k_fieldprep<double>, grid, block, 0, s, field_args<double>(c, fields), bd);
+        launch_fields<double>(c, s, fields);
     else
-        hipLaunchKernelGGL(k_fieldprep<float>, grid, block, 0, s, field_args<float>(c, fields), bd);
+        launch_fields<float>(c, s, fields);
 }
 
 // Event pair around a phase when timing is on.
