@@ -287,8 +287,9 @@ int mhdpic_deposit_read(mhdpic_ctx* ctx, int64_t* out, int32_t reset_accumulated
  * of particles that have left their box (absorbing faces, mhdpic_remove_tagged)
  * read NaN.  MHDPIC_ESTATE once particles were added (mhdpic_inject): use
  * mhdpic_particles_read_ids.  Does not wait.  Works through the context's
- * workspace: a later call of this context on another stream that does so too
- * (a step, an injection, a read-out) is made to wait for it on the device. */
+ * workspace: a later call of this context that does so too (a step, an
+ * injection, a read-out), on whatever stream, is made to wait for it on the
+ * device. */
 int mhdpic_particles_read(mhdpic_ctx* ctx, double* x, double* v, void* hip_stream);
 
 /* Particles in their boxes (Sec. 5 runs add and remove particles): writes

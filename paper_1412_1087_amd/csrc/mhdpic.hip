@@ -250,11 +250,10 @@ struct mhdpic_ctx {
     // a one-call advance: its first binning keeps the error word that set-up
     // left (Layout::err_first), and a set one keeps the read-outs from writing
     bool one_call = false;
-    // a read-out that uses the other particle buffer: work enqueued on another
-    // stream that also does waits for read_event first (wait_for_read)
+    // a read-out that uses the other particle buffer: later work that also does
+    // waits for read_event first (wait_for_read)
     std::mutex read_mu;
     hipEvent_t read_event = nullptr;
-    hipStream_t read_stream = nullptr;
     bool read_pending = false;
     // cached graph of mhdpic_step_graph
     hipGraphExec_t graph_exec = nullptr;
@@ -921,17 +920,25 @@ int post_error_copy(mhdpic_ctx* c, hipStream_t s) {
 }
 
 // Orders the work that a call is about to enqueue on s after a read-out that
-// was enqueued on another stream and uses the other particle buffer.  The
-// caller holds read_mu.
+// uses the other particle buffer.  On the read-out's own stream the wait adds
+// nothing, but equal handles do not tell that it is the same one: each thread
+// has its own hipStreamPerThread, and a new stream may get a destroyed one's
+// handle.  The caller holds read_mu.
 int wait_for_read(mhdpic_ctx* c, hipStream_t s) {
-    if (c->read_pending && s != c->read_stream) HIP_TRY(hipStreamWaitEvent(s, c->read_event, 0));
-    c->read_pending = false;
+    if (c->read_pending) HIP_TRY(hipStreamWaitEvent(s, c->read_event, 0));
     return MHDPIC_OK;
 }
 
 int lock_and_wait_for_read(mhdpic_ctx* c, hipStream_t s) {
     std::lock_guard<std::mutex> lock(c->read_mu);
     return wait_for_read(c, s);
+}
+
+// A call that has waited has enqueued its work: what follows that work follows
+// the read-out too.  (After a call that fails, the next one still waits.)
+void read_passed(mhdpic_ctx* c) {
+    std::lock_guard<std::mutex> lock(c->read_mu);
+    c->read_pending = false;
 }
 
 // Checks the arguments of a step call against the boxes (move limit per box).
@@ -1556,6 +1563,7 @@ int mhdpic_step_sub(mhdpic_ctx* c, const double* B, const double* vg, const doub
     c->codes_fresh = false;
     if (rc) return rc;
     if (capturing) return MHDPIC_OK;
+    read_passed(c);
     c->codes_fresh = true;
     c->codes_dt.assign(dt, dt + c->nb);
     c->codes_nsub = n_sub;
@@ -1608,6 +1616,7 @@ int mhdpic_step_graph_sub(mhdpic_ctx* c, const double* B, const double* vg, cons
         c->graph_key = key;  // n_steps is even: the buffers end as they began
     }
     HIP_TRY(hipGraphLaunch(c->graph_exec, s));
+    read_passed(c);
     c->tail = 0;  // its binnings took in any added particles
     c->codes_fresh = true;
     c->codes_dt.assign(dt, dt + c->nb);
@@ -1872,7 +1881,6 @@ int mhdpic_particles_read(mhdpic_ctx* c, double* x, double* v, void* hip_stream)
     rc = read_particles(c, x, v, true, s);
     if (rc) return rc;
     HIP_TRY(hipEventRecord(c->read_event, s));
-    c->read_stream = s;
     c->read_pending = true;
     return MHDPIC_OK;
 }
@@ -1999,6 +2007,7 @@ int mhdpic_inject(mhdpic_ctx* c, const int64_t* n_new, const double* x, const do
     rc = launch_deposit(c, s, job);
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
+    read_passed(c);
     return read_error_now(c, s);
 }
 
