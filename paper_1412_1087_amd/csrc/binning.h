@@ -19,19 +19,16 @@ namespace mhdpic {
 
 // Code words for this call's dt (the push computes them for the later steps
 // of the call): next_code of each particle's stored state, with the
-// operations of the step's first half drift.  err_first, if given, receives
-// the error word as the work before this kernel left it (a one-call advance
-// reports what its set-up latched, and writes no outputs then).
+// operations of the step's first half drift.
 template <class Pol, int NDIM>
 __global__ void __launch_bounds__(256)
 k_rekey_items(typename Pol::Part P, uint16_t* __restrict__ code, uint32_t* __restrict__ cnt,
               const WorkItem* __restrict__ items, const uint32_t* __restrict__ n_items,
-              const BoxDev* __restrict__ boxes, uint32_t* err, uint32_t* err_first) {
+              const BoxDev* __restrict__ boxes, uint32_t* err) {
     using R = typename Pol::R;
     constexpr int K = Codes<NDIM>::K;
     __shared__ uint32_t s_cnt[K];
     uint32_t item;
-    if (err_first && blockIdx.x == 0 && threadIdx.x == 0) *err_first = atomicAdd(err, 0u);
     if (!item_of_block(n_items, item)) return;
     const WorkItem w = items[item];
     const BoxDev bx = boxes[w.box];

@@ -163,7 +163,9 @@ struct Layout {
     // offsets into the workspace
     size_t partA = 0, partB = 0, part_bytes = 0;
     size_t key = 0, code = 0, EB = 0, Dcorr = 0, nJ0 = 0, nJ1 = 0;
-    size_t count = 0, cursor = 0, tile_box = 0, err = 0, err_first = 0;
+    size_t count = 0, cursor = 0, tile_box = 0;
+    size_t err = 0;             // what kernels have latched
+    size_t err_setup = 0;       // what a one-call advance's set-up has
     size_t items[2] = {0, 0}, n_items[2] = {0, 0}, item_first[2] = {0, 0};
     size_t used = 0;            // slots the last sort or binning filled
     size_t plan = 0;            // PlanShare: the ticket, then a word per block
@@ -247,9 +249,11 @@ struct mhdpic_ctx {
     int32_t codes_nsub = 0;
     int32_t next_id = 0;  // id of the next added particle
     bool absorbs = false; // a box has an absorbing face
-    // a one-call advance: its first binning keeps the error word that set-up
-    // left (Layout::err_first), and a set one keeps the read-outs from writing
+    // a one-call advance that does not wait for its set-up: the set-up latches
+    // its errors in a word of its own (Layout::err_setup), and a set one keeps
+    // the read-outs from writing
     bool one_call = false;
+    bool in_setup = false;
     // a read-out that uses the other particle buffer: later work that also does
     // waits for read_event first (wait_for_read)
     std::mutex read_mu;
@@ -370,8 +374,8 @@ Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
     L.off = take((size_t)L.NW * L.K * 4);
     L.plan = take(8 + 8 * (size_t)plan_blocks(L.NT) + 4 + 4 + 4);
     L.err = L.plan + 8 + 8 * (size_t)plan_blocks(L.NT);
-    L.err_first = L.err + 4;
-    L.used = L.err_first + 4;
+    L.err_setup = L.err + 4;
+    L.used = L.err_setup + 4;
     L.boxes = take((size_t)nb * sizeof(BoxDev));
     L.part_off = take((size_t)(nb + 1) * 8);
     L.cell_off = take((size_t)(nb + 1) * 8);
@@ -423,6 +427,13 @@ template <typename T>
 T* at(mhdpic_ctx* c, size_t off) {
     return reinterpret_cast<T*>(c->ws + off);
 }
+
+// The word that set-up's kernels latch errors in, and those of later work.
+uint32_t* err_word(mhdpic_ctx* c) {
+    return at<uint32_t>(c, c->one_call && c->in_setup ? c->L.err_setup : c->L.err);
+}
+// A one-call advance's set-up errors, which its read-outs look at.
+const uint32_t* refused(mhdpic_ctx* c) { return c->one_call ? at<uint32_t>(c, c->L.err_setup) : nullptr; }
 
 unsigned grid_for(int64_t n, int block) {
     int64_t g = (n + block - 1) / block;
@@ -513,8 +524,7 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fields)
     if (keys == kKeysRekey)
         hipLaunchKernelGGL((k_rekey_items<Pol, NDIM>), dim3(item_grid(L)), dim3(256), 0, s, A,
                            at<uint16_t>(c, L.code), at<uint32_t>(c, L.cnt), at<WorkItem>(c, L.items[it]),
-                           at<uint32_t>(c, L.n_items[it]), bd, at<uint32_t>(c, L.err),
-                           c->one_call ? at<uint32_t>(c, L.err_first) : nullptr);
+                           at<uint32_t>(c, L.n_items[it]), bd, at<uint32_t>(c, L.err));
     else if (keys == kKeysStay)
         hipLaunchKernelGGL((k_stay_items<PS, NDIM>), dim3(item_grid(L)), dim3(256), 0, s, A,
                            at<uint16_t>(c, L.code), at<uint32_t>(c, L.cnt), at<WorkItem>(c, L.items[it]),
@@ -627,7 +637,7 @@ int launch_first_sort(mhdpic_ctx* c, hipStream_t s, const NewArrays& in) {
         hipLaunchKernelGGL((k_init_records<NDIM, PS>), dim3(sh.grid), dim3(256), sh.hbytes, s, rec, in.x, in.v,
                            in.m, in.qm, at<uint32_t>(c, L.key), at<uint32_t>(c, L.count),
                            at<BoxDev>(c, L.boxes), SlotBoxes{at<int64_t>(c, L.part_off), c->nb}, L.N0, L.NT,
-                           sh.chunk, at<uint32_t>(c, L.err));
+                           sh.chunk, err_word(c));
     launch_scan(c, s, 0, false);
     if (L.N0 > 0) {
         hipLaunchKernelGGL(k_init_rank, dim3(sh.grid), dim3(256), sh.hbytes, s, P.pid, at<uint32_t>(c, L.key),
@@ -775,7 +785,7 @@ int launch_deposit_pol(mhdpic_ctx* c, hipStream_t s, const DepositJob& job, int 
     hipLaunchKernelGGL(kern, dim3(item_grid(L)), dim3(BLOCK), lds, s,
                        part<typename Pol::Part, R>(c, c->cur),
                        at<int64_t>(c, c->nj == 0 ? L.nJ0 : L.nJ1), L.NC, at<BoxDev>(c, L.boxes),
-                       job.items, job.n_items, at<uint32_t>(c, L.err), job.t_cut, job.t_now,
+                       job.items, job.n_items, err_word(c), job.t_cut, job.t_now,
                        c->grp_shape.size() > 1 ? grp : -1);
     return MHDPIC_OK;
 }
@@ -1181,7 +1191,7 @@ void launch_convert(mhdpic_ctx* c, hipStream_t s, const double* x, const double*
     const Layout& L = c->L;
     const BoxDev* bd = at<BoxDev>(c, L.boxes);
     const int64_t* po = at<int64_t>(c, L.part_off);
-    uint32_t* err = at<uint32_t>(c, L.err);
+    uint32_t* err = err_word(c);
     const unsigned g = grid_for(n, 256);
     if (c->precision == MHDPIC_FP64) {
         PartF64 P = part<PartF64, double>(c, buf);
@@ -1235,6 +1245,7 @@ int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const
         if (nb > kBoxArgs) hipLaunchKernelGGL(k_put_boxes, dim3(1), dim3(256), 0, s, bd, chunk, b0, nc);
     }
     c->dt_uploaded = dt != nullptr;
+    c->in_setup = true;
     // cleared: the accumulated deposits and n_CR, J_CR (neighbours in the
     // workspace), the tile counts, and plan, error word and slots
     const auto words = [](size_t bytes) { return (int64_t)(bytes / 8); };
@@ -1266,6 +1277,7 @@ int init_device(mhdpic_ctx* c, const mhdpic_box* boxes, const int64_t* np, const
         rc = launch_init_deposit(c, s);
         if (rc) return rc;
     }
+    c->in_setup = false;
     HIP_TRY(hipGetLastError());
     return wait ? read_error_now(c, s) : MHDPIC_OK;
 }
@@ -1289,7 +1301,7 @@ void launch_read(mhdpic_ctx* c, double* x, double* v, bool records, hipStream_t 
         if (may_leave(c)) fill_u32(reinterpret_cast<uint32_t*>(rec), N * (int64_t)(sizeof(*rec) / 4), kDeadCell, s);
         hipLaunchKernelGGL((k_read_records<NDIM, PS>), dim3(item_grid(L)), dim3(256), 0, s, P, rec, items, ni);
         hipLaunchKernelGGL((k_read_columns<NDIM, T>), dim3(grid_for(N, 256)), dim3(256), 0, s, rec, x, v, bd,
-                           N, nan, c->one_call ? at<uint32_t>(c, L.err_first) : nullptr);
+                           N, nan, refused(c));
         return;
     }
     const unsigned gf = (unsigned)std::min<int64_t>(grid_for(3 * N, 256), 8192);
@@ -1325,7 +1337,7 @@ int read_deposits(mhdpic_ctx* c, int64_t* out, bool clear, hipStream_t s) {
     if (n == 0) return MHDPIC_OK;
     int64_t* nJ = at<int64_t>(c, c->nj == 0 ? c->L.nJ0 : c->L.nJ1);
     int64_t* D = at<int64_t>(c, c->L.Dcorr);
-    const uint32_t* skip = c->one_call ? at<uint32_t>(c, c->L.err_first) : nullptr;
+    const uint32_t* skip = refused(c);
     const auto grid = [](int64_t m) { return dim3((unsigned)std::min<int64_t>(grid_for(m, 256), 8192)); };
     if ((uintptr_t)out % 16 == 0)  // (n is a multiple of four: so is the second half)
         hipLaunchKernelGGL(k_deposit_read<longlong2>, grid(n / 2), dim3(256), 0, s, (longlong2*)out,
