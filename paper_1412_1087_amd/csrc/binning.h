@@ -191,7 +191,9 @@ __device__ __forceinline__ void plan_prefix(const PlanShare& ps, uint32_t t, uin
 // The plan of a binning, from the counts of every (item, code) group: slots
 // and work items for each destination tile, both in tile order, and the offset
 // of each arriving group (in the order of TileGroups), with the totals in
-// *used and *n_items_next.  One wave per tile; the blocks add up their tiles
+// *used and *n_items_next.  If refused is given and *refused set, the plan is of
+// no particles and ends the current list too: the binning's and the push's
+// kernels that follow, of all steps of the call, find no items.  One wave per tile; the blocks add up their tiles
 // and find the sums before them as they go (plan_prefix).  Bound by the
 // latency of its few dependent loads: one launch of 10 us in place of a count,
 // a scan of all tiles in one block and the offsets (a binning of the 64^3 box,
@@ -206,11 +208,13 @@ k_bin_plan(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_f
            uint32_t* __restrict__ off, const int32_t* __restrict__ tile_box,
            const BoxDev* __restrict__ boxes, uint32_t* __restrict__ item_first_next,
            WorkItem* __restrict__ items_next, uint32_t* __restrict__ n_items_next,
-           uint32_t* __restrict__ used, PlanShare ps, int NT, int P) {
+           uint32_t* __restrict__ n_items, uint32_t* __restrict__ used, PlanShare ps, int NT, int P,
+           const uint32_t* refused) {
     constexpr int K = Codes<NDIM>::K;
     constexpr int NWV = kPlanBlock / 64;
-    __shared__ uint32_t s_slots[NWV], s_items[NWV], s_t, s_par;
+    __shared__ uint32_t s_slots[NWV], s_items[NWV], s_t, s_par, s_stop;
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+    if (threadIdx.x == 64) s_stop = refused ? *refused : 0u;  // (beside the ticket, by another wave)
     if (threadIdx.x == 0) {
         const unsigned long long n = atomicAdd(ps.ticket, 1ull);
         s_t = (uint32_t)(n % gridDim.x);
@@ -220,11 +224,13 @@ k_bin_plan(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_f
     const uint32_t t = s_t;
     const int d = (int)t * NWV + wave;           // this wave's tile
     const bool has = d < NT;                     // (whole wave)
+    const bool stop = s_stop != 0;
     TileGroups<NDIM> tg;
+    tg.total = 0;
     uint32_t c0 = 0, to0 = 0;  // the lane's first group: its particles, its offset's place
     uint32_t tot = 0;
     int32_t box = 0;
-    if (has) {
+    if (has && !stop) {
         box = tile_box[d];
         tg.load(boxes[box], d, item_first, lane);
         for (uint32_t g0 = 0; g0 < tg.total; g0 += 64) {  // the same trip count in every lane
@@ -257,6 +263,7 @@ k_bin_plan(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_f
             *used = sb + ta;
             *n_items_next = ib + tb;
             item_first_next[NT] = ib + tb;
+            if (stop) *n_items = 0;
         }
         if (lane < NWV) {
             s_slots[lane] = sb + x - a;

@@ -589,12 +589,13 @@ struct FieldArgs {
     const int64_t* cell_off;
     int nb;
     int64_t NC;
+    const uint32_t* refused;  // nothing to do if given and set
 };
 
 template <typename TF>
 __device__ __forceinline__ void fieldprep_cell(const FieldArgs<TF>& fa, const BoxDev* boxes, int64_t c) {
     const int64_t NC = fa.NC;
-    if (c >= NC) return;
+    if (c >= NC || (fa.refused && *fa.refused)) return;
     const double* __restrict__ B = fa.B;
     const double* __restrict__ vg = fa.vg;
     const double* __restrict__ rho = fa.rho;

@@ -250,8 +250,8 @@ struct mhdpic_ctx {
     int32_t next_id = 0;  // id of the next added particle
     bool absorbs = false; // a box has an absorbing face
     // a one-call advance that does not wait for its set-up: the set-up latches
-    // its errors in a word of its own (Layout::err_setup), and a set one keeps
-    // the read-outs from writing
+    // its errors in a word of its own (Layout::err_setup), and a set one ends
+    // the steps at the first binning and keeps the read-outs from writing
     bool one_call = false;
     bool in_setup = false;
     // a read-out that uses the other particle buffer: later work that also does
@@ -432,7 +432,7 @@ T* at(mhdpic_ctx* c, size_t off) {
 uint32_t* err_word(mhdpic_ctx* c) {
     return at<uint32_t>(c, c->one_call && c->in_setup ? c->L.err_setup : c->L.err);
 }
-// A one-call advance's set-up errors, which its read-outs look at.
+// A one-call advance's set-up errors, which its steps and read-outs look at.
 const uint32_t* refused(mhdpic_ctx* c) { return c->one_call ? at<uint32_t>(c, c->L.err_setup) : nullptr; }
 
 unsigned grid_for(int64_t n, int block) {
@@ -501,6 +501,7 @@ FieldArgs<T> field_args(mhdpic_ctx* c, const StepFields& f) {
     fa.cell_off = at<int64_t>(c, L.cell_off);
     fa.nb = c->nb;
     fa.NC = L.NC;
+    fa.refused = refused(c);
     return fa;
 }
 
@@ -533,9 +534,10 @@ int launch_bin(mhdpic_ctx* c, hipStream_t s, int keys, const StepFields* fields)
                        at<uint32_t>(c, L.cnt), at<uint32_t>(c, L.item_first[it]),
                        at<uint32_t>(c, L.off), at<int32_t>(c, L.tile_box), bd,
                        at<uint32_t>(c, L.item_first[1 - it]), at<WorkItem>(c, L.items[1 - it]),
-                       at<uint32_t>(c, L.n_items[1 - it]), at<uint32_t>(c, L.used),
+                       at<uint32_t>(c, L.n_items[1 - it]), at<uint32_t>(c, L.n_items[it]),
+                       at<uint32_t>(c, L.used),
                        PlanShare{at<unsigned long long>(c, L.plan), at<unsigned long long>(c, L.plan + 8)},
-                       L.NT, L.P);
+                       L.NT, L.P, refused(c));
     // where the particles move (mhdpic_set_particle_moves): in the push, the
     // binning only leaves a map to their slots, through which the push reads
     // the particles and writes them, updated, to the other buffer; a compaction
@@ -1367,10 +1369,11 @@ int advance_impl(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* np, in
     if ((c.L.N0 > 0 && (!x_out || !v_out)) || (c.L.NC > 0 && !dep_out))
         return fail(MHDPIC_EINVAL, "x_out, v_out or deposits_out is NULL");
     c.last_stream = s;
-    // with steps to follow, the host does not wait for set-up: the kernels run
+    // with steps to follow, the host does not wait for set-up, which took a
+    // 37x29 box's advance of two steps from 180 to 157 us.  The first rekey runs
     // on any state (out-of-range cells are clamped, offsets that are not finite
-    // move nothing), so what set-up refuses is found at the end; a 64^2 box's
-    // advance went from 180 to 157 us
+    // move nothing); after set-up has refused the input, the plan leaves the
+    // steps nothing to do, and its error is returned at the end
     c.one_call = n_steps > 0;
     rc = init_device(&c, boxes, np, dt, n_sub, x, v, m, qm, s, nullptr, !c.one_call);
     if (rc) return rc;
