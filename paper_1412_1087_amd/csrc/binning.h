@@ -247,7 +247,7 @@ k_bin_plan(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_f
         }
         for (int o = 32; o > 0; o >>= 1) tot += (uint32_t)__shfl_xor((int)tot, o);
     }
-    const uint32_t ni = (tot + (uint32_t)P - 1) / (uint32_t)P;  // items of even size
+    const uint32_t ni = (tot + (uint32_t)P - 1) / (uint32_t)P;  // items
     if (lane == 0) {
         s_slots[wave] = tot;
         s_items[wave] = ni;
@@ -288,11 +288,12 @@ k_bin_plan(const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ item_f
         run += (uint32_t)__shfl((int)x, 63);
     }
     if (lane == 0) item_first_next[d] = io;
+    const EvenItems ev(tot, ni);
     for (uint32_t k = (uint32_t)lane; k < ni; k += 64) {
         WorkItem w;
         w.tile = d;
-        w.begin = (int32_t)(s0 + (uint32_t)((uint64_t)tot * k / ni));
-        w.end = (int32_t)(s0 + (uint32_t)((uint64_t)tot * (k + 1) / ni));
+        w.begin = (int32_t)(s0 + ev.begin(k));
+        w.end = (int32_t)(s0 + ev.begin(k + 1));
         w.box = box;
         items_next[io + k] = w;
     }

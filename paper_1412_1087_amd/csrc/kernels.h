@@ -354,6 +354,19 @@ struct SlotBoxes {
     __device__ __forceinline__ int box(int64_t j) const { return find_box(off, nb, j); }
 };
 
+// n particles of a tile in ni items of even size (ni may be 0): item k begins
+// at particle begin(k).  One division a tile: a thread of k_scan goes over all
+// items of its tiles, and with a 64-bit product and quotient for each bound the
+// set-up of 4.2 million particles in one tile (1024 items) took 716 us, not 553.
+struct EvenItems {
+    uint32_t size, rest;
+    __device__ __forceinline__ EvenItems(uint32_t n, uint32_t ni) {
+        size = n / max(ni, 1u);
+        rest = n - size * ni;
+    }
+    __device__ __forceinline__ uint32_t begin(uint32_t k) const { return k * size + min(k, rest); }
+};
+
 // Exclusive scan of tile counts and the work list: each tile's particles are
 // split into items of at most P particles; items name slots from base on.
 // *total receives the particles.  One block of 1024 threads.
@@ -389,12 +402,13 @@ k_scan(const uint32_t* __restrict__ count, uint32_t* __restrict__ cursor,
         uint32_t c = count[i];
         cursor[i] = off;
         item_first[i] = io;
-        const uint32_t ni = (c + (uint32_t)P - 1) / (uint32_t)P;  // of even size
+        const uint32_t ni = (c + (uint32_t)P - 1) / (uint32_t)P;
+        const EvenItems ev(c, ni);
         for (uint32_t k = 0; k < ni; ++k) {
             WorkItem w;
             w.tile = i;
-            w.begin = (int32_t)(base + off + (uint32_t)((uint64_t)c * k / ni));
-            w.end = (int32_t)(base + off + (uint32_t)((uint64_t)c * (k + 1) / ni));
+            w.begin = (int32_t)(base + off + ev.begin(k));
+            w.end = (int32_t)(base + off + ev.begin(k + 1));
             w.box = tile_box[i];
             items[io++] = w;
         }
