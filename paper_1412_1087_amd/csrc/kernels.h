@@ -761,26 +761,30 @@ __global__ void k_read_particles(PS P, double* __restrict__ x, double* __restric
 
 // The same read-out through records: k_read_records writes each particle's
 // state to the record of its id, and k_read_columns turns the records into the
-// columns (or does nothing if skip is given and *skip set).  Ids lie at random against slots, and a store of 8 bytes then costs
-// as much as one of a half or whole 64-byte line; k_read_particles has six of
-// them per particle, and its outputs a fill before.  A record is half a line
-// (binary32) or one (binary64), written by one lane, in the other particle
-// buffer, which holds nothing between calls and has 36 (64) bytes a slot at
-// least.  Measured: 3.1 M particles 278 and 469 us (binary32, binary64), with
-// records 189 and 259; 4.2 M in the 64^3 box 574 and 349; 16.8 M 3817 and 1364;
-// 0.5 M 80 and 37.
+// columns (or does nothing if skip is given and *skip set).  Ids lie at random
+// against slots, and a store of 8 bytes then costs as much as one of a half or
+// whole 64-byte line; k_read_particles has six of them per particle, and its
+// outputs a fill before.  A record is half a line (binary32) or one (binary64),
+// written by one lane, in the other particle buffer, which holds nothing between
+// calls and has 36 (64) bytes a slot at least.  Measured: 3.1 M particles 278 and
+// 469 us (binary32, binary64), with records 189 and 259; 4.2 M in the 64^3 box 574
+// and 349; 16.8 M 3817 and 1364; 0.5 M 80 and 37.
+//
+// Where particles may have left, a record that none has written must be told
+// from the others: by a byte that k_read_records sets in `here` if given, else by
+// its cell, which is kDeadCell in records filled beforehand (see launch_read).
 template <typename R>
 struct __attribute__((aligned(16))) ReadRec {
     R d[3], v[3];
-    uint32_t cell;  // kDeadCell: no particle has written it
+    uint32_t cell;
     int32_t box;
 };
 static_assert(sizeof(ReadRec<float>) == 32 && sizeof(ReadRec<double>) == 64, "record sizes");
 
 template <int NDIM, typename PS>
 __global__ void __launch_bounds__(256)
-k_read_records(PS P, ReadRec<typename PS::R>* __restrict__ rec, const WorkItem* __restrict__ items,
-               const uint32_t* __restrict__ n_items) {
+k_read_records(PS P, ReadRec<typename PS::R>* __restrict__ rec, uint8_t* __restrict__ here,
+               const WorkItem* __restrict__ items, const uint32_t* __restrict__ n_items) {
     uint32_t item;
     if (!item_of_block(n_items, item)) return;
     const WorkItem w = items[item];
@@ -793,20 +797,23 @@ k_read_records(PS P, ReadRec<typename PS::R>* __restrict__ rec, const WorkItem* 
             r.d[d] = d < NDIM ? P.d[d][j] : typename PS::R(0);
             r.v[d] = P.v[d][j];
         }
-        rec[P.pid[j]] = r;
+        const int32_t p = P.pid[j];
+        rec[p] = r;
+        if (here) here[p] = 1;
     }
 }
 
 template <int NDIM, typename R>
 __global__ void __launch_bounds__(256)
-k_read_columns(const ReadRec<R>* __restrict__ rec, double* __restrict__ x, double* __restrict__ v,
-               const BoxDev* __restrict__ boxes, int64_t N, double nan, const uint32_t* skip) {
+k_read_columns(const ReadRec<R>* __restrict__ rec, const uint8_t* __restrict__ here,
+               double* __restrict__ x, double* __restrict__ v, const BoxDev* __restrict__ boxes,
+               int64_t N, double nan, const uint32_t* skip) {
     if (skip && *skip) return;
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= N) return;
     const ReadRec<R> r = rec[p];
     double xx[3] = {nan, nan, nan}, vv[3] = {nan, nan, nan};
-    if (r.cell != kDeadCell) {
+    if (here ? here[p] != 0 : r.cell != kDeadCell) {
         const BoxDev& bx = boxes[r.box];
         int i[3];
         unpack_cell<NDIM>(r.cell, i[0], i[1], i[2]);
