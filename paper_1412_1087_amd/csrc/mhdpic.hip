@@ -142,13 +142,14 @@ struct DefaultTiles {
 // pay: wanting 512 of them, a 32^3 box with 16 per cell (256 tiles of 2048)
 // went from 108 to 121 us a step.
 constexpr int64_t kItemsWanted = 256;
+constexpr int32_t kSmallestItems = 512;
 int32_t item_particles(const std::vector<std::pair<int64_t, int64_t>>& boxes) {
-    for (int32_t P = kItemParticles; P > 512; P /= 2) {
+    for (int32_t P = kItemParticles; P > kSmallestItems; P /= 2) {
         int64_t items = 0;
         for (const auto& b : boxes) items += b.first * ((b.second + b.first * P - 1) / (b.first * P));
         if (items >= kItemsWanted) return P;
     }
-    return 512;
+    return kSmallestItems;
 }
 
 // Blocks of k_bin_plan over NT tiles.
@@ -321,8 +322,9 @@ int validate_boxes(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
     return MHDPIC_OK;
 }
 
+// items: particles per work item; 0: by item_particles
 Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32_t precision,
-                   int ndim, const std::vector<TileShape>& tiles, bool large_items = false) {
+                   int ndim, const std::vector<TileShape>& tiles, int32_t items = 0) {
     Layout L;
     std::vector<std::pair<int64_t, int64_t>> sizes;
     for (int b = 0; b < nb; ++b) {
@@ -339,7 +341,7 @@ Layout make_layout(const mhdpic_box* boxes, int32_t nb, const int64_t* np, int32
     }
     // work items: one per tile and one per P slots, and as many again for a
     // tail of added particles in contexts with a capacity
-    L.P = large_items ? kItemParticles : item_particles(sizes);
+    L.P = items ? items : item_particles(sizes);
     L.NW = L.NT + (int32_t)(L.N / L.P) + 1;
     if (L.tagged) L.NW = 2 * L.NW;
     const size_t N = (size_t)L.N, NC = (size_t)L.NC;
@@ -1136,7 +1138,7 @@ int open_context(mhdpic_ctx* c, const mhdpic_box* boxes, int32_t n_boxes, const 
     if (ws_bytes < L.total) {
         rc = validate_boxes(boxes, n_boxes, np, precision, ndim, tiles, true);
         if (rc) return rc;
-        L = make_layout(boxes, n_boxes, np, precision, ndim, tiles, true);
+        L = make_layout(boxes, n_boxes, np, precision, ndim, tiles, kItemParticles);
     }
     if (ws_bytes < L.total) return fail(MHDPIC_ENOMEM, "workspace too small");
     if (L.N0 > 0 && (!x || !v || !m || !qm)) return fail(MHDPIC_EINVAL, "particle arrays are NULL");
@@ -1541,7 +1543,7 @@ int mhdpic_advance_noalloc(const mhdpic_box* boxes, int32_t n_boxes, const int64
     std::vector<TileShape> tiles;
     int rc = validate_boxes(boxes, n_boxes, n_particles, precision, ndim, tiles, true);
     if (rc) return rc;
-    const size_t need = make_layout(boxes, n_boxes, n_particles, precision, ndim, tiles, true).total;
+    const size_t need = make_layout(boxes, n_boxes, n_particles, precision, ndim, tiles, kItemParticles).total;
     if (need > kScratchBytes) {
         std::snprintf(g_last_error, sizeof(g_last_error),
                       "mhdpic_advance_noalloc: these boxes and particles need %zu bytes of scratch; "
@@ -1731,7 +1733,9 @@ int mhdpic_autotune_classes_workspace_size(const mhdpic_box* boxes, int32_t n_bo
     size_t best = 0;
     int rc = mhdpic_autotune_workspace_size(boxes, n_boxes, n_particles, precision, &best);
     if (rc) return rc;
-    // the mix with the most tiles: each box with its candidate of most tiles
+    // the mix with the most tiles: each box with its candidate of most tiles, in
+    // the smallest items, so that it bounds every mix (one of fewer tiles may get
+    // smaller items and more of them)
     const int ndim = boxes[0].ndim;
     std::vector<mhdpic_box> b(boxes, boxes + n_boxes);
     for (mhdpic_box& B : b) {
@@ -1747,9 +1751,11 @@ int mhdpic_autotune_classes_workspace_size(const mhdpic_box* boxes, int32_t n_bo
             }
         }
     }
-    size_t sz = 0;
-    rc = mhdpic_workspace_size(b.data(), n_boxes, n_particles, precision, &sz);
+    int nd;
+    std::vector<TileShape> tiles;
+    rc = validate_boxes(b.data(), n_boxes, n_particles, precision, nd, tiles);
     if (rc) return rc;
+    const size_t sz = make_layout(b.data(), n_boxes, n_particles, precision, nd, tiles, kSmallestItems).total;
     *bytes = std::max(best, sz);
     return MHDPIC_OK;
 }
