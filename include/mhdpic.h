@@ -331,7 +331,9 @@ int mhdpic_remove_tagged(mhdpic_ctx* ctx, double t_cut, double t_now, void* hip_
  * MHDPIC_OK, MHDPIC_ENONFINITE, MHDPIC_ERANGE or MHDPIC_ESTATE. */
 int mhdpic_check(mhdpic_ctx* ctx, void* hip_stream);
 
-/* Frees the context's host-side state.  The workspace is the caller's. */
+/* Frees the context's host-side state.  The workspace is the caller's.  Waits
+ * for the context's last steps and mhdpic_particles_read calls (not for those
+ * captured into a caller's graph). */
 int mhdpic_destroy(mhdpic_ctx* ctx);
 
 /* Message for the last non-OK code returned on the calling thread. */

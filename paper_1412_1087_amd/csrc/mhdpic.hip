@@ -1918,12 +1918,12 @@ int mhdpic_particles_read(mhdpic_ctx* c, double* x, double* v, void* hip_stream)
     HIP_TRY(hipStreamIsCapturing(s, &cap));
     // (a captured read-out is replayed where no wait orders it against other
     // streams' calls: it writes to its outputs only)
-    if (cap != hipStreamCaptureStatusNone || read_straight(c)) return read_particles(c, x, v, false, s);
+    if (cap != hipStreamCaptureStatusNone) return read_particles(c, x, v, false, s);
     std::lock_guard<std::mutex> lock(c->read_mu);
     int rc = wait_for_read(c, s);
     if (rc) return rc;
     if (!c->read_event) HIP_TRY(hipEventCreateWithFlags(&c->read_event, hipEventDisableTiming));
-    rc = read_particles(c, x, v, true, s);
+    rc = read_particles(c, x, v, !read_straight(c), s);
     if (rc) return rc;
     HIP_TRY(hipEventRecord(c->read_event, s));
     c->read_pending = true;
@@ -2144,7 +2144,10 @@ int mhdpic_destroy(mhdpic_ctx* c) {
         (void)hipEventSynchronize(c->err_event);
         (void)hipEventDestroy(c->err_event);
     }
-    if (c->read_event) (void)hipEventDestroy(c->read_event);
+    if (c->read_event) {  // (a read-out writes to the workspace, which is the caller's from here on)
+        (void)hipEventSynchronize(c->read_event);
+        (void)hipEventDestroy(c->read_event);
+    }
     if (c->err_host) (void)hipHostFree(c->err_host);
     delete c;
     return MHDPIC_OK;
