@@ -160,8 +160,11 @@ int mhdpic_advance(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* n_pa
  * bit.  The call's scratch is a static device array of 64 MiB per GPU, held
  * from the library's first use on that GPU until the process ends; the call
  * itself calls no allocating routine.  Boxes and particles whose workspace
- * (mhdpic_workspace_size) exceeds 64 MiB are rejected with MHDPIC_ENOMEM
- * before any device work.  Every call on one GPU uses the same scratch, so
+ * exceeds 64 MiB are rejected with MHDPIC_ENOMEM before any device work.  That
+ * is the least workspace mhdpic_advance serves them with, the layout of the
+ * largest default tiles and work items; for contexts of few tiles it is
+ * smaller than mhdpic_workspace_size, whose layout is used where it fits.
+ * Every call on one GPU uses the same scratch, so
  * calls that overlap on one GPU (other threads, other streams) race: the
  * caller must serialise them.  Waits for the stream. */
 int mhdpic_advance_noalloc(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* n_particles,
@@ -349,6 +352,9 @@ const char* mhdpic_last_error(void);
  * (MHDPIC_TIMING_ALL: all four); 0 stops; other values are EINVAL.  Each
  * recorded event costs some microseconds of stream time, so time only the
  * phases you need.  Launches inside a graph capture are never timed.
+ * With phase 0 or 1 timed, the field preparation runs in a launch of its own;
+ * otherwise it shares the last launch of the step's first binning.  The sum of
+ * the phases is then the time of a step launched apart, not of an untimed one.
  * mhdpic_timing_read waits for the recorded events, writes the summed
  * milliseconds and the number of timed launches of each phase (ms[4],
  * launches[4]) and clears the record. */

@@ -195,10 +195,12 @@ __device__ __forceinline__ void plan_prefix(const PlanShare& ps, uint32_t t, uin
 // no particles and ends the current list too: the binning's and the push's
 // kernels that follow, of all steps of the call, find no items.  One wave per tile; the blocks add up their tiles
 // and find the sums before them as they go (plan_prefix).  Bound by the
-// latency of its few dependent loads: one launch of 10 us in place of a count,
-// a scan of all tiles in one block and the offsets (a binning of the 64^3 box,
-// 2048 tiles, went from 39 to 33 us, of the 128^3 one, 32768 tiles, from 409 to
-// 315, and a step of a 32^2 box from 47 to 40).  (Slots given out in the order in
+// latency of its few dependent loads.  Kernel times against the three launches
+// of a count, a scan of all tiles in one block and the offsets: 2048 tiles of the
+// 64^3 box 10.4 us and 16, 32768 of the 128^3 box 55 and 156; on the strip, where
+// a tenth of 512 tiles have some sixty items each, 18.8 and 21.6.
+// With the gaps between launches a binning of the 64^3 box went from 39 to 33 us,
+// of the 128^3 one from 409 to 315, and a step of a 32^2 box from 47 to 40.  (Slots given out in the order in
 // which the blocks come would save the prefix, but the push then runs
 // neighbouring tiles, whose particles share lines of memory, far apart in time
 // and on other XCDs: on the shock strip it went from 140 to 180 us.)
@@ -394,7 +396,15 @@ constexpr int kMapChunk2D = MHDPIC_MAP_CHUNK_2D;
 // us together, 29 and 57 apart), and a small
 // step is one launch shorter.  In the plan's launch instead, whose few waves
 // wait on one load after another, the plan took as long as the streaming made
-// its loads wait: 84 us there.
+// its loads wait: 84 us there.  A scatter that moves the particles takes the
+// fields too: 8192 x 256 cells with 2 M particles 262 us a step, 278 with the
+// fields apart, 1024^2 with 4 per cell 345 and 356, 32^2 31 and 34, 128^3 with 8 per
+// cell 2277 and 2296, 64^3 with 24 per cell 795 and 827; a few sizes lose (64^3 with
+// 16 per cell 531 and 524 us, 512^2 with 8 209 and 202).  So do 2D boxes of 2.5 M
+// cells and more with fewer than one particle in ten cells, spread over all tiles,
+// where the items' many short blocks hold field blocks up (2048^2, one in a
+// hundred: 411 and 378 us); the shock box with as few, which lie in a few
+// tiles, gains (110 and 114).
 template <int NDIM, typename PS, int BLOCK, bool TAGGED, bool MAP>
 __global__ void __launch_bounds__(BLOCK)
 k_bin_scatter_class(PS A, PS Bo, const uint16_t* __restrict__ code, const uint32_t* __restrict__ off,

@@ -80,10 +80,11 @@ __global__ void k_fill_i64(int64_t* p, int64_t n) {
 }
 
 // The deposits read out: n elements of nJ to out, and as many of D after them,
-// with D cleared if `clear`; nothing if skip is given and *skip set.  V: the widest access out is aligned to (a pair
-// at a time, or its two halves).  One launch, bound by memory, in place of two
-// copies and a fill: 2.1 M cells (8192 x 256) took 72 us and take 53,
-// and a step of a 32^2 box with its read-out went from 39.5 to 35.5 us.
+// with D cleared if `clear`; nothing if skip is given and *skip set.  V: the
+// widest access out is aligned to (a pair at a time, or its two halves).  One
+// launch, bound by memory, in place of two copies and a fill: 2.1 M cells
+// (8192 x 256) took 72 us and take 53, and a step of a 32^2 box with its read-out
+// went from 39.5 to 35.5 us.
 template <typename V>
 __global__ void __launch_bounds__(256)
 k_deposit_read(V* __restrict__ out, const V* __restrict__ nJ, V* __restrict__ D, int64_t n, bool clear,
@@ -128,8 +129,9 @@ struct ClearArgs {
 // in `a`, which are then written there): first particle and first cell of each
 // box (with the totals at index nb), the box of every tile, and the cleared
 // memory.  One launch in place of an upload that the host waited for, the
-// tables and a fill per array: a one-call advance of a 64^2 box went from 217
-// to 177 us, of a 3D one with 8 steps of 1.2 M particles from 874 to 834.
+// tables and a fill per array: a one-call advance of two steps of a 37 x 29 box
+// went from 217 to 177 us, of a 40 x 33 x 27 one with 8 particle steps of 0.32 M
+// particles from 874 to 834.
 __global__ void __launch_bounds__(256)
 k_setup(BoxDev* __restrict__ boxes, BoxArgs a, bool put, int nb, int64_t* __restrict__ part_off,
         int64_t* __restrict__ cell_off, int32_t* __restrict__ tile_box, int NT, ClearArgs ca) {
