@@ -164,9 +164,8 @@ int mhdpic_advance(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* n_pa
  * is the least workspace mhdpic_advance serves them with, the layout of the
  * largest default tiles and work items; for contexts of few tiles it is
  * smaller than mhdpic_workspace_size, whose layout is used where it fits.
- * Every call on one GPU uses the same scratch, so
- * calls that overlap on one GPU (other threads, other streams) race: the
- * caller must serialise them.  Waits for the stream. */
+ * Every call on one GPU uses the same scratch: calls of several threads take
+ * turns.  Waits for the stream. */
 int mhdpic_advance_noalloc(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* n_particles,
                            int32_t precision, const double* x, const double* v, const double* m,
                            const double* qm, const double* B, const double* vg, const double* rho,

@@ -1402,12 +1402,13 @@ int advance_impl(const mhdpic_box* boxes, int32_t n_boxes, const int64_t* np, in
     // steps nothing to do, and its error is returned at the end
     c.one_call = n_steps > 0;
     rc = init_device(&c, boxes, np, dt, n_sub, x, v, m, qm, s, nullptr, !c.one_call);
-    if (rc) return rc;
-    if (n_steps > 0) rc = enqueue_steps(&c, B, vg, rho, n_steps, n_sub, s, false);
+    if (!rc && n_steps > 0) rc = enqueue_steps(&c, B, vg, rho, n_steps, n_sub, s, false);
     if (!rc) rc = read_particles(&c, x_out, v_out, true, s);
     if (!rc) rc = read_deposits(&c, dep_out, false, s);
-    if (rc) return rc;
-    HIP_TRY(hipGetLastError());
+    if (rc) {  // (what was enqueued still uses the workspace)
+        (void)hipStreamSynchronize(s);
+        return rc;
+    }
     // (what set-up latched comes before what the steps did with such a state)
     uint32_t bits[2] = {0, 0};
     HIP_TRY(hipMemcpyAsync(bits, c.ws + c.L.err, sizeof(bits), hipMemcpyDeviceToHost, s));
@@ -1429,23 +1430,27 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 namespace {
 
 constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-void* g_scratch_ptr[kMaxDevices] = {};
+struct Scratch {
+    std::mutex mu;  // held by the call that uses the scratch
+    void* p = nullptr;
+};
+Scratch g_scratch[kMaxDevices];
 
-// Address of the current device's scratch, looked up on the first call on
+// The current device's scratch, its address looked up on the first call on
 // that device, with it current, and kept.
-int scratch_address(void** out) {
+int lock_scratch(std::unique_lock<std::mutex>& lock, void** out) {
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return fail(MHDPIC_ENOTSUP, "device index beyond 63");
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[dev]) {
+    Scratch& sc = g_scratch[dev];
+    lock = std::unique_lock<std::mutex>(sc.mu);
+    if (!sc.p) {
         void* p = nullptr;
         HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
         if (!p) return fail(MHDPIC_EDEVICE, "hipGetSymbolAddress returned no address for the scratch");
-        g_scratch_ptr[dev] = p;
+        sc.p = p;
     }
-    *out = g_scratch_ptr[dev];
+    *out = sc.p;
     return MHDPIC_OK;
 }
 
@@ -1551,8 +1556,12 @@ int mhdpic_advance_noalloc(const mhdpic_box* boxes, int32_t n_boxes, const int64
                       need, kScratchBytes);
         return MHDPIC_ENOMEM;
     }
+    // calls of several threads take turns: each returns when its stream has
+    // passed its work (overlapping ones would set up the scratch under each
+    // other's kernels, whose waits for words in it might then not end)
     void* ws = nullptr;
-    rc = scratch_address(&ws);
+    std::unique_lock<std::mutex> lock;
+    rc = lock_scratch(lock, &ws);
     if (rc) return rc;
     return advance_impl(boxes, n_boxes, n_particles, precision, x, v, m, qm, B, vg, rho, dt,
                         n_steps, n_sub, x_out, v_out, deposits_out, ws, kScratchBytes,
